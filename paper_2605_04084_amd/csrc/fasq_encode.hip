@@ -17,6 +17,8 @@
 //     the ids, packed in the library's id format.
 // Exact integer sums make the result independent of the order in which the
 // atomics land: the encoder is deterministic.
+#include <type_traits>
+
 #include "fasq_device.h"
 #include "fasq_internal.h"
 
@@ -24,10 +26,17 @@ namespace fasq {
 
 namespace {
 
-constexpr int kEncThreads = 256;
-constexpr int kEncPointsPerThread = 4;
-constexpr int kEncTileFloats = 16384;                // codeword tile in LDS: 64 KB of fp32
-constexpr int kEncAggBytes = 64 * 1024;              // per-workgroup cluster sums in LDS, when they fit
+constexpr int kEncThreads = 512;                     // 8 waves
+constexpr int kEncWaves = kEncThreads / kWave;
+constexpr int kEncSuper = 64;                        // codewords per superblock (two MFMA tiles)
+constexpr int kEncTileBytes = 64 * 1024;             // codewords and norms in LDS (two workgroups per CU)
+constexpr int kEncDirectThreads = 256;
+constexpr int kEncDirectPoints = 4;
+constexpr int kEncDirectMax = 64;                    // codewords up to which every distance is evaluated
+constexpr int kEncFineMax = 512;                     // codewords up to which the MFMA kernel keeps blocks of 8
+constexpr int kEncSumThreads = 1024;
+constexpr int kEncSumBytes = 150 * 1024;             // LDS for the cluster sums of a workgroup
+constexpr int kEncSumMaxRanges = 8;                  // passes over the points the tables are worth
 constexpr float kQScale = 16777216.0f;               // 2^24
 constexpr double kQInv = 1.0 / 16777216.0;
 
@@ -71,123 +80,456 @@ __global__ void k_enc_zero(int64_t* __restrict__ p, int64_t n) {
 }
 
 // Squared distance in fp32, operations in the defined order, no contraction.
-template <int D>
-__device__ __forceinline__ float sq_dist(const float* p, const float* c, int d) {
+// The padding of both vectors is zero: it adds +0 to a sum that is never -0,
+// so the bits are those of the d real components.
+template <int DP>
+__device__ __forceinline__ float sq_dist(const float* p, const float* c) {
 #pragma clang fp contract(off)
   float acc = 0.f;
-  if constexpr (D > 0) {
 #pragma unroll
-    for (int i = 0; i < D; ++i) {
-      const float diff = p[i] - c[i];
-      acc = acc + diff * diff;
-    }
-  } else {
-    for (int i = 0; i < d; ++i) {
-      const float diff = p[i] - c[i];
-      acc = acc + diff * diff;
-    }
+  for (int i = 0; i < DP; ++i) {
+    const float diff = p[i] - c[i];
+    acc = acc + diff * diff;
   }
   return acc;
 }
 
-// Assignment of every point to its nearest codeword; with ACCUM the points'
-// exact fixed-point values and counts are added to the cluster sums (through
-// a per-workgroup LDS table when AGG).  D = 0: runtime d <= 16.
-template <int D, bool ACCUM, bool AGG>
-__global__ __launch_bounds__(kEncThreads) void k_enc_assign(const half_t* __restrict__ w, int64_t P, int d,
-                                                            const half_t* __restrict__ cb, int C,
-                                                            uint32_t* __restrict__ assign,
-                                                            int64_t* __restrict__ sums,
-                                                            int64_t* __restrict__ counts) {
-  constexpr int DM = D > 0 ? D : 16;
-  constexpr int PPT = kEncPointsPerThread;
-  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  float* tile = reinterpret_cast<float*>(smem);                       // [ct][d] fp32 codewords
-  int64_t* agg = reinterpret_cast<int64_t*>(smem + kEncTileFloats * 4);  // [C][d + 1] sums, counts
-  const int dd = D > 0 ? D : d;
-  const int ct = kEncTileFloats / dd;  // codewords per tile
-  const int ntiles = (C + ct - 1) / ct;
+// Codewords in LDS: DP halves each (d padded with zeros), 64 to a superblock,
+// and one unused read's worth after each superblock, so that lanes that read
+// the same place of different superblocks spread over the banks.
+template <int DP>
+struct EncTile {
+  static constexpr int CW = DP * 2;                                   // bytes per codeword
+  static constexpr int SB = kEncSuper * CW + (CW < 16 ? CW : 16);     // bytes per superblock
+  static constexpr int PER = SB + kEncSuper * 4;                      // with its norms
+  static constexpr int MAX = kEncTileBytes / PER * kEncSuper;         // codewords per tile
+  __device__ static uint32_t at(int k) { return (uint32_t)(k / kEncSuper) * SB + (uint32_t)(k % kEncSuper) * CW; }
+};
 
-  if constexpr (AGG) {
-    for (int i = threadIdx.x; i < C * (dd + 1); i += blockDim.x) agg[i] = 0;
+template <int DP>
+__device__ __forceinline__ void lds_codeword(const uint8_t* tile, int k, float* c) {
+  const uint8_t* q = tile + EncTile<DP>::at(k);
+  half_t v[DP];
+  if constexpr (DP == 2) *reinterpret_cast<uint32_t*>(v) = *reinterpret_cast<const uint32_t*>(q);
+  else if constexpr (DP == 4) *reinterpret_cast<u32x2*>(v) = *reinterpret_cast<const u32x2*>(q);
+  else {
+#pragma unroll
+    for (int j = 0; j < DP / 8; ++j) reinterpret_cast<u32x4*>(v)[j] = reinterpret_cast<const u32x4*>(q)[j];
   }
+#pragma unroll
+  for (int i = 0; i < DP; ++i) c[i] = static_cast<float>(v[i]);
+}
 
-  const int64_t group = (int64_t)kEncThreads * PPT;
-  bool staged = false;
+template <int DP>
+__device__ __forceinline__ void global_vector(const half_t* __restrict__ src, int64_t k, int d, float* c) {
+  if (d == DP) {  // one wide load
+#pragma unroll
+    for (int i = 0; i < DP; ++i) c[i] = static_cast<float>(src[k * DP + i]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < DP; ++i) c[i] = i < d ? static_cast<float>(src[k * d + i]) : 0.f;
+  }
+}
+
+// Assignment of every point to its nearest codeword, every distance
+// evaluated: for codebooks up to kEncDirectMax, where the fixed work of the
+// MFMA kernel per tile of points exceeds it.  One thread takes
+// kEncDirectPoints points; the codebook is fp32 in LDS, read by broadcast.
+// With ACCUM the cluster sums and counts gather in an LDS table on the way.
+template <int DP, bool ACCUM>
+__global__ __launch_bounds__(kEncDirectThreads) void k_enc_direct(const half_t* __restrict__ w, int64_t P, int d,
+                                                                  const half_t* __restrict__ cb, int C,
+                                                                  uint32_t* __restrict__ assign,
+                                                                  unsigned long long* __restrict__ sums,
+                                                                  unsigned long long* __restrict__ counts) {
+  constexpr int PPT = kEncDirectPoints;
+  __shared__ float tile[kEncDirectMax * DP];
+  __shared__ unsigned long long agg[ACCUM ? kEncDirectMax * (DP + 1) : 1];  // [C][d + 1] sums, count
+  if constexpr (ACCUM) {
+    for (int i = threadIdx.x; i < C * (d + 1); i += blockDim.x) agg[i] = 0;
+  }
+  for (int i = threadIdx.x; i < C * DP; i += blockDim.x)
+    tile[i] = i % DP < d ? static_cast<float>(cb[(int64_t)(i / DP) * d + i % DP]) : 0.f;
+  __syncthreads();
+  const int64_t group = (int64_t)kEncDirectThreads * PPT;
   for (int64_t g0 = blockIdx.x * group; g0 < P; g0 += (int64_t)gridDim.x * group) {
-    float pv[PPT][DM];
+    float pv[PPT][DP];
     float best[PPT];
     uint32_t bk[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-      const int64_t p = g0 + (int64_t)j * kEncThreads + threadIdx.x;
-      const int64_t pc = p < P ? p : P - 1;
-#pragma unroll
-      for (int i = 0; i < DM; ++i) pv[j][i] = (i < dd) ? static_cast<float>(w[pc * dd + i]) : 0.f;
+      const int64_t p = g0 + (int64_t)j * kEncDirectThreads + threadIdx.x;
+      global_vector<DP>(w, p < P ? p : P - 1, d, pv[j]);
       best[j] = __builtin_inff();
       bk[j] = 0;
     }
-    for (int t = 0; t < ntiles; ++t) {
-      const int k0 = t * ct;
-      const int nk = C - k0 < ct ? C - k0 : ct;
-      if (!(staged && ntiles == 1)) {
-        __syncthreads();  // everyone is done with the previous tile
-        for (int i = threadIdx.x; i < nk * dd; i += blockDim.x) tile[i] = static_cast<float>(cb[(int64_t)k0 * dd + i]);
-        __syncthreads();
-        staged = true;
-      }
-      for (int k = 0; k < nk; ++k) {
-        const float* c = tile + k * dd;
+    for (int k = 0; k < C; ++k) {
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) {
-          const float dist = sq_dist<D>(pv[j], c, dd);
-          if (dist < best[j]) {  // strict: the lowest index keeps a tie
-            best[j] = dist;
-            bk[j] = (uint32_t)(k0 + k);
+      for (int j = 0; j < PPT; ++j) {
+        const float dist = sq_dist<DP>(pv[j], tile + k * DP);
+        if (dist < best[j]) {  // strict: the lowest index keeps a tie
+          best[j] = dist;
+          bk[j] = (uint32_t)k;
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < PPT; ++j) {
+      const int64_t p = g0 + (int64_t)j * kEncDirectThreads + threadIdx.x;
+      if (p >= P) continue;
+      assign[p] = bk[j];
+      if constexpr (ACCUM) {
+        unsigned long long* t = agg + bk[j] * (d + 1);
+#pragma unroll
+        for (int i = 0; i < DP; ++i)
+          if (i < d) atomicAdd(t + i, (unsigned long long)(int64_t)(pv[j][i] * kQScale));  // exact
+        atomicAdd(t + d, 1ull);
+      }
+    }
+  }
+  if constexpr (ACCUM) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < C * (d + 1); i += blockDim.x) {
+      const int k = i / (d + 1), c = i - k * (d + 1);
+      if (agg[i] != 0) atomicAdd(c < d ? &sums[k * d + c] : &counts[k], agg[i]);
+    }
+  }
+}
+
+// Assignment of every point to its nearest codeword on the matrix cores.
+//
+// The defined distance costs 3 d + 2 vector operations per (point, codeword)
+// pair.  Instead the matrix cores give s = |c|^2 / 2 - p.c, which orders the
+// codewords like the distance up to a bounded error, and the defined distance
+// is evaluated only where that error leaves a choice:
+//   * v_mfma_f32_32x32x16_f16 with 32 codewords as rows, 32 points as columns
+//     and the norms |c|^2 / 2 as the C operand.  Lane l holds column l % 32
+//     and 16 of the rows, in SUB blocks of 16 / SUB codewords; a block's
+//     minimum takes one v_min3 for two codewords.  Each lane keeps the
+//     smallest block minimum b1, its block, and the second smallest b2.
+//   * Every codeword that can win has s <= min s + tau.  A lane whose b1 lies
+//     in that range evaluates the defined distance of that block's codewords;
+//     the two lanes of a point are merged by (distance, id).
+//   * If b2 lies in the range too (or the minimum is not finite), the point's
+//     whole codebook is evaluated: by the wave together for a few points, by
+//     each point's two lanes for many.
+// tau: fp32 sums of d + 1 terms differ from the exact s by at most
+// (d + 2) 2^-22 (|p| + |c|)^2 / 2 whatever the order and rounding of the
+// additions (one ulp each), and the defined distance from the exact one by
+// (d + 3) 2^-24 of itself.  For the codewords that matter |c| <= |p| + dist
+// and dist^2 = |p|^2 + 2 s, so R = 2.01 |p| + 1.01 dist bounds |p| + |c| (the
+// margins cover the error of dist itself) and tau = R^2 (d + 3) 2^-21.
+// Non-finite codewords can never win (their distance is inf or NaN): they
+// are staged as zeros with an infinite norm.
+// Bound by vector issue: per MFMA (32 cycles) 8 v_min3 (4 cycles each) and 3
+// more instructions, which overlap the matrix core by about half only.
+// Measured, 4096 x 4096, d = 4, C = 4096 (17.2 G pairs): 0.66-0.75 ms per
+// assignment, every distance evaluated 4.7 ms; d = 2, C = 256: 0.20 against
+// 0.44 ms; d = 8, C = 256: 0.08 against 0.26 ms; d = 16, C = 256: 0.07 against
+// 4.9 ms (a run-time d); d = 4, C = 65536 (256 rows): 1.7 against 9.7 ms.
+// At C = 64 the two are even (d = 2: 0.15 against 0.11 ms every distance,
+// d = 8: 0.083 both, d = 1: 0.28 against 0.22), hence kEncDirectMax.  Blocks
+// of 8 (SUB = 2) halve the final evaluation, which outweighs the minima up to
+// 512 codewords.
+// FN: tiles of 32 points per wave (each codeword fragment and its norms serve
+// all of them).  ONE: the codebook is one LDS tile; else it is staged tile by
+// tile for every group of points, and the final evaluation reads L2.
+template <int DP, int FN, int SUB, bool ONE>
+__global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __restrict__ w, int64_t P, int d,
+                                                               const half_t* __restrict__ cb, int C,
+                                                               uint32_t* __restrict__ assign) {
+  using Tile = EncTile<DP>;
+  constexpr int BL = 16 / SUB;  // codewords per block and lane
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int tile_cap = ONE ? (C + kEncSuper - 1) / kEncSuper * kEncSuper : Tile::MAX;  // codewords per tile
+  const int ntiles = ONE ? 1 : (C + tile_cap - 1) / tile_cap;
+  uint8_t* cw = smem;
+  float* norms = reinterpret_cast<float*>(smem + (tile_cap / kEncSuper * Tile::SB + 15) / 16 * 16);
+  int* odd = reinterpret_cast<int*>(norms + tile_cap);  // ONE: the tile holds padding or non-finite codewords
+
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int h = lane >> 5, col = lane & 31;
+  const float inf = __builtin_inff();
+
+  auto stage = [&](int k0, int nk) {  // codewords [k0, k0 + nk), padded to whole superblocks
+    const int n = (nk + kEncSuper - 1) / kEncSuper * kEncSuper;
+    for (int k = threadIdx.x; k < n; k += blockDim.x) {
+      float c[DP];
+      float norm = 0.f;
+      bool ok = k < nk;
+      global_vector<DP>(cb, k0 + (k < nk ? k : 0), d, c);
+#pragma unroll
+      for (int i = 0; i < DP; ++i) {
+        norm = __builtin_fmaf(c[i], c[i], norm);
+        ok = ok && __builtin_fabsf(c[i]) < inf;
+      }
+      uint8_t* q = cw + Tile::at(k);
+#pragma unroll
+      for (int i = 0; i < DP; i += 2) {
+        half2_t v;
+        v[0] = ok ? static_cast<half_t>(c[i]) : static_cast<half_t>(0.f);
+        v[1] = ok ? static_cast<half_t>(c[i + 1]) : static_cast<half_t>(0.f);
+        *reinterpret_cast<uint32_t*>(q + i * 2) = as_u32(v);
+      }
+      norms[k] = ok ? 0.5f * norm : inf;
+      if (ONE && !ok) *odd = 1;
+    }
+  };
+  // the codeword fragment of rows [k, k + 32) of the tile: K values 8 h .. 8 h + 7
+  auto read_rows = [&](int k) {
+    u32x4 v = u32x4{0u, 0u, 0u, 0u};
+    const uint8_t* q = cw + Tile::at(k) + col * Tile::CW;
+    if constexpr (DP == 16) {
+      v = *reinterpret_cast<const u32x4*>(q + 16 * h);
+    } else if (h == 0) {
+      if constexpr (DP == 2) v[0] = *reinterpret_cast<const uint32_t*>(q);
+      else if constexpr (DP == 4) {
+        const u32x2 t = *reinterpret_cast<const u32x2*>(q);
+        v[0] = t[0]; v[1] = t[1];
+      } else v = *reinterpret_cast<const u32x4*>(q);
+    }
+    return __builtin_bit_cast(half8_t, v);
+  };
+  auto read_norms = [&](int k) {  // rows (i / 4) * 8 + 4 h + i % 4 of the tile at k
+    float16_t n;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float4_t t = *reinterpret_cast<const float4_t*>(norms + k + 8 * j + 4 * h);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) n[4 * j + i] = t[i];
+    }
+    return n;
+  };
+  auto row_of = [&](int i) { return (i / 4) * 8 + 4 * h + i % 4; };  // i in [0, 16)
+
+  if constexpr (ONE) {
+    if (threadIdx.x == 0) *odd = 0;
+    __syncthreads();
+    stage(0, C);
+    __syncthreads();
+  }
+  const bool check = ONE && *odd != 0;
+  // opaque infinities: minima that start from one take three operands from
+  // the first step on (v_min3 throughout), and the median with the other is
+  // the minimum of two values without the instruction that quiets a NaN
+  float top = inf, bottom = -inf;
+  asm volatile("" : "+v"(top), "+v"(bottom));
+
+  const int64_t group = (int64_t)kEncWaves * FN * 32;
+  for (int64_t g0 = blockIdx.x * group; g0 < P; g0 += (int64_t)gridDim.x * group) {
+    const int64_t p0 = g0 + (int64_t)wave * FN * 32;  // first point of the wave
+    // B operands: the negated points (K values past d are zero)
+    half8_t b[FN];
+    float b1[FN], b2[FN];
+    int i1[FN];
+#pragma unroll
+    for (int f = 0; f < FN; ++f) {
+      const int64_t p = p0 + f * 32 + col;
+      const int64_t pc = p < P ? p : P - 1;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) b[f][i] = static_cast<half_t>(0.f);
+      if (DP == 16 || h == 0) {
+#pragma unroll
+        for (int i = 0; i < (DP < 8 ? DP : 8); ++i) {
+          const int c = DP == 16 ? 8 * h + i : i;
+          if (c < d) b[f][i] = -w[pc * d + c];
+        }
+      }
+      b1[f] = b2[f] = inf;
+      i1[f] = 0;
+    }
+    for (int t = 0; t < ntiles; ++t) {
+      const int k0 = t * tile_cap;
+      const int nk = C - k0 < tile_cap ? C - k0 : tile_cap;
+      if constexpr (!ONE) {
+        __syncthreads();  // everyone is done with the previous tile
+        stage(k0, nk);
+        __syncthreads();
+      }
+      for (int k = 0; k < nk; k += 32) {
+        const half8_t a = read_rows(k);
+        const float16_t n = read_norms(k);
+        const int blk = (k0 + k) / 32 * SUB;
+#pragma unroll
+        for (int f = 0; f < FN; ++f) {
+          const float16_t s = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b[f], n, 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < SUB; ++j) {
+            float v = top;
+#pragma unroll
+            for (int i = 0; i < BL; i += 2) v = __builtin_fminf(__builtin_fminf(v, s[j * BL + i]), s[j * BL + i + 1]);
+            i1[f] = v < b1[f] ? blk + j : i1[f];
+            b2[f] = __builtin_amdgcn_fmed3f(v, b1[f], b2[f]);
+            b1[f] = __builtin_amdgcn_fmed3f(v, b1[f], bottom);
           }
         }
       }
     }
 #pragma unroll
-    for (int j = 0; j < PPT; ++j) {
-      const int64_t p = g0 + (int64_t)j * kEncThreads + threadIdx.x;
-      if (p >= P) continue;
-      assign[p] = bk[j];
-      if constexpr (ACCUM) {
-        const uint32_t k = bk[j];
-        for (int i = 0; i < dd; ++i) {
-          const int64_t q = (int64_t)(pv[j][i] * kQScale);  // exact: an integer below 2^31
-          if constexpr (AGG) atomicAdd(reinterpret_cast<unsigned long long*>(&agg[k * (dd + 1) + i]),
-                                       (unsigned long long)q);
-          else atomicAdd(reinterpret_cast<unsigned long long*>(&sums[(int64_t)k * dd + i]), (unsigned long long)q);
+    for (int f = 0; f < FN; ++f) {
+      const int64_t p = p0 + f * 32 + col;
+      float pv[DP];
+      global_vector<DP>(w, p < P ? p : P - 1, d, pv);
+      float pn = 0.f;
+#pragma unroll
+      for (int i = 0; i < DP; ++i) pn = __builtin_fmaf(pv[i], pv[i], pn);
+      const float gb = __builtin_fminf(b1[f], __shfl_xor(b1[f], 32, kWave));
+      const float r = 2.01f * __builtin_sqrtf(pn) + 1.01f * __builtin_sqrtf(__builtin_fmaxf(pn + 2.f * gb, 0.f));
+      const float thr = gb + r * r * ((float)(d + 3) * 4.76837158203125e-7f);  // 2^-21
+      // not (x < y): true for NaN as well
+      const bool slow = !(__builtin_fabsf(gb) < inf) || !(b2[f] > thr);
+      float best = inf;
+      uint32_t bk = 0;
+      auto consider = [&](int k) {  // strict: the lowest index keeps a tie
+        float c[DP];
+        if constexpr (ONE) lds_codeword<DP>(cw, k, c);
+        else global_vector<DP>(cb, k, d, c);
+        const float dist = sq_dist<DP>(pv, c);
+        // (an infinite norm in LDS: padding, or a codeword staged as zeros)
+        if (dist < best && (!check || norms[k] < inf)) {
+          best = dist;
+          bk = (uint32_t)k;
         }
-        if constexpr (AGG) atomicAdd(reinterpret_cast<unsigned long long*>(&agg[k * (dd + 1) + dd]), 1ull);
-        else atomicAdd(reinterpret_cast<unsigned long long*>(&counts[k]), 1ull);
+      };
+      uint64_t todo = __ballot(slow);
+      todo = (todo | (todo >> 32)) & 0xFFFFFFFFull;  // points of the tile
+      const bool many = __popcll(todo) > 20;
+      if (many) {
+        for (int k = 0; k < C; k += 32)
+          for (int i = 0; i < 16; ++i) consider(ONE || k + row_of(i) < C ? k + row_of(i) : C - 1);
+      } else if (b1[f] <= thr) {
+        const int k = i1[f] / SUB * 32, i0 = i1[f] % SUB * BL;
+        if (!ONE || check) {
+          for (int i = 0; i < BL; ++i) {
+            const int kk = k + (i0 / 4) * 8 + row_of(i);  // i0 is a multiple of 4
+            consider(ONE || kk < C ? kk : C - 1);
+          }
+        } else {
+          // reads in batches, then selects: no branch and one wait per batch
+          constexpr int RB = DP == 16 ? 4 : BL < 8 ? BL : 8;
+#pragma unroll
+          for (int j = 0; j < BL; j += RB) {
+            float c[RB][DP];
+#pragma unroll
+            for (int i = 0; i < RB; ++i) lds_codeword<DP>(cw, k + (i0 / 4) * 8 + row_of(j + i), c[i]);
+#pragma unroll
+            for (int i = 0; i < RB; ++i) {
+              const float dist = sq_dist<DP>(pv, c[i]);
+              bk = dist < best ? (uint32_t)(k + (i0 / 4) * 8 + row_of(j + i)) : bk;
+              best = dist < best ? dist : best;
+            }
+          }
+        }
       }
+      if (!many) {
+        while (todo) {  // one point at a time, the codewords dealt to the lanes
+          const int j = __ffsll((unsigned long long)todo) - 1;
+          todo &= todo - 1;
+          float keep[DP];
+          const float kbest = best;
+          const uint32_t kbk = bk;
+#pragma unroll
+          for (int i = 0; i < DP; ++i) {
+            keep[i] = pv[i];
+            pv[i] = __shfl(pv[i], j, kWave);
+          }
+          best = inf;
+          bk = 0;
+          for (int k = lane; k < C; k += kWave) consider(k);
+#pragma unroll
+          for (int m = 1; m < kWave; m *= 2) {
+            const float ob = __shfl_xor(best, m, kWave);
+            const uint32_t ok = (uint32_t)__shfl_xor((int)bk, m, kWave);
+            if (ob < best || (ob == best && ok < bk)) { best = ob; bk = ok; }
+          }
+          const bool mine = col == j;
+          best = mine ? best : kbest;
+          bk = mine ? bk : kbk;
+#pragma unroll
+          for (int i = 0; i < DP; ++i) pv[i] = keep[i];
+        }
+      }
+      const float ob = __shfl_xor(best, 32, kWave);
+      const uint32_t ok = (uint32_t)__shfl_xor((int)bk, 32, kWave);
+      if (ob < best || (ob == best && ok < bk)) bk = ok;
+      if (p < P && h == 0) assign[p] = bk;
     }
   }
-  if constexpr (ACCUM && AGG) {
-    __syncthreads();
-    for (int k = threadIdx.x; k < C; k += blockDim.x) {
-      const int64_t cnt = agg[k * (dd + 1) + dd];
-      if (cnt == 0) continue;
-      for (int i = 0; i < dd; ++i)
-        atomicAdd(reinterpret_cast<unsigned long long*>(&sums[(int64_t)k * dd + i]),
-                  (unsigned long long)agg[k * (dd + 1) + i]);
-      atomicAdd(reinterpret_cast<unsigned long long*>(&counts[k]), (unsigned long long)cnt);
+}
+
+// Cluster sums (values times 2^24: exact integers) and counts of the assigned
+// points.  Workgroup (x, y) takes its share x of the points and the clusters
+// [y cap, y cap + cap), gathers them in LDS (`copies` tables, dealt to the
+// waves, where few clusters would make many lanes meet in one) and adds its
+// table to the global sums.  cap = 0: every point straight to global memory.
+// 4096 x 4096, d = 4, C = 4096: 60 us in one table per CU, 270 us with every
+// point's atomics in global memory.
+// D: d as a compile-time constant, with w aligned to D halves; 0: any d.
+template <int D>
+__global__ __launch_bounds__(kEncSumThreads) void k_enc_sum(const half_t* __restrict__ w, int64_t P, int rt_d, int C,
+                                                            int cap, int copies, const uint32_t* __restrict__ assign,
+                                                            unsigned long long* __restrict__ sums,
+                                                            unsigned long long* __restrict__ counts) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int d = D > 0 ? D : rt_d;
+  const int k0 = blockIdx.y * cap;
+  const int nk = C - k0 < cap ? C - k0 : cap;
+  unsigned long long* tsum = reinterpret_cast<unsigned long long*>(smem);            // [copies][cap][d]
+  uint32_t* tcnt = reinterpret_cast<uint32_t*>(smem + (size_t)copies * cap * d * 8);  // [copies][cap]
+  for (int i = threadIdx.x; i < copies * cap * d; i += blockDim.x) tsum[i] = 0;
+  for (int i = threadIdx.x; i < copies * cap; i += blockDim.x) tcnt[i] = 0;
+  __syncthreads();
+  const int mine = cap > 0 ? (int)(threadIdx.x / kWave) % copies * cap : 0;
+  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < P; p += (int64_t)gridDim.x * blockDim.x) {
+    const uint32_t k = assign[p];
+    half_t v[D > 0 ? D : 16];
+    if constexpr (D == 2) *reinterpret_cast<uint32_t*>(v) = reinterpret_cast<const uint32_t*>(w)[p];
+    else if constexpr (D == 4) *reinterpret_cast<u32x2*>(v) = reinterpret_cast<const u32x2*>(w)[p];
+    else if constexpr (D == 8) *reinterpret_cast<u32x4*>(v) = reinterpret_cast<const u32x4*>(w)[p];
+    else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (i < d) v[i] = w[p * d + i];
+    }
+    const uint32_t t = k - (uint32_t)k0;
+    if (cap > 0 && t >= (uint32_t)nk) continue;
+#pragma unroll
+    for (int i = 0; i < (D > 0 ? D : 16); ++i) {
+      if (i >= d) continue;
+      const unsigned long long q = (unsigned long long)(int64_t)(static_cast<float>(v[i]) * kQScale);  // exact
+      if (cap > 0) atomicAdd(&tsum[(mine + (int)t) * d + i], q);
+      else atomicAdd(&sums[(int64_t)k * d + i], q);
+    }
+    if (cap > 0) atomicAdd(&tcnt[mine + (int)t], 1u);
+    else atomicAdd(&counts[k], 1ull);
+  }
+  if (cap == 0) return;
+  __syncthreads();
+  for (int i = threadIdx.x; i < nk * (d + 1); i += blockDim.x) {
+    unsigned long long v = 0;
+    if (i < nk * d) {
+      for (int c = 0; c < copies; ++c) v += tsum[c * cap * d + i];
+      if (v != 0) atomicAdd(&sums[(int64_t)k0 * d + i], v);
+    } else {
+      for (int c = 0; c < copies; ++c) v += tcnt[c * cap + i - nk * d];
+      if (v != 0) atomicAdd(&counts[k0 + i - nk * d], v);
     }
   }
 }
 
 // New codewords: each non-empty cluster's rounded mean; empty ones are kept.
-__global__ void k_enc_update(uint16_t* __restrict__ cb, const int64_t* __restrict__ sums,
-                             const int64_t* __restrict__ counts, int C, int d) {
-  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < (int64_t)C * d;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t k = t / d;
-    const int64_t cnt = counts[k];
-    if (cnt == 0) continue;
+// The sums and counts are cleared for the next iteration.
+__global__ void k_enc_update(uint16_t* __restrict__ cb, int64_t* __restrict__ sums, int64_t* __restrict__ counts,
+                             int C, int d) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= C) return;
+  const int64_t cnt = counts[k];
+  if (cnt == 0) return;
+  counts[k] = 0;
+  for (int i = 0; i < d; ++i) {
+    const int64_t t = (int64_t)k * d + i;
     const double mean = (static_cast<double>(sums[t]) * kQInv) / static_cast<double>(cnt);
+    sums[t] = 0;
     cb[t] = f64_to_f16_rne(mean);
   }
 }
@@ -224,36 +566,95 @@ inline unsigned grid_for(int64_t n, int threads) {
   return (unsigned)(g < 65536 ? (g > 0 ? g : 1) : 65536);
 }
 
-template <int D>
-hipError_t launch_assign_d(const half_t* w, int64_t P, int d, const half_t* cb, int C, uint32_t* assign,
-                           int64_t* sums, int64_t* counts, bool accum, const DeviceInfo& dev, hipStream_t stream) {
-  const int dd = D > 0 ? D : d;
-  const bool agg = accum && (int64_t)C * (dd + 1) * 8 <= kEncAggBytes;
-  const int lds = kEncTileFloats * 4 + (agg ? C * (dd + 1) * 8 : 0);
-  const int64_t groups = (P + (int64_t)kEncThreads * kEncPointsPerThread - 1) / ((int64_t)kEncThreads * kEncPointsPerThread);
-  // enough workgroups to fill the chip; more would only repeat the codebook staging and the LDS flushes
-  int64_t blocks = 4 * (int64_t)dev.num_cus;
-  if (blocks > groups) blocks = groups;
-  if (blocks < 1) blocks = 1;
+template <int DP>
+hipError_t launch_direct(const half_t* w, int64_t P, int d, const half_t* cb, int C, uint32_t* assign, int64_t* sums,
+                         int64_t* counts, bool accum, const DeviceInfo& dev, hipStream_t stream) {
+  const int64_t per = (int64_t)kEncDirectThreads * kEncDirectPoints;
+  const int64_t groups = (P + per - 1) / per, slots = 4 * (int64_t)dev.num_cus;
+  const dim3 grid((unsigned)(groups < slots ? groups : slots));
+  unsigned long long* s = reinterpret_cast<unsigned long long*>(sums);
+  unsigned long long* c = reinterpret_cast<unsigned long long*>(counts);
+  if (accum) return launch_kernel(k_enc_direct<DP, true>, grid, dim3(kEncDirectThreads), 0, stream, w, P, d, cb, C, assign, s, c);
+  return launch_kernel(k_enc_direct<DP, false>, grid, dim3(kEncDirectThreads), 0, stream, w, P, d, cb, C, assign, s, c);
+}
+
+template <int DP>
+hipError_t launch_assign_dp(const half_t* w, int64_t P, int d, const half_t* cb, int C, uint32_t* assign,
+                            const DeviceInfo& dev, hipStream_t stream) {
+  using Tile = EncTile<DP>;
+  const bool one = C <= Tile::MAX;
+  const int cap = one ? (C + kEncSuper - 1) / kEncSuper * kEncSuper : Tile::MAX;
+  const int lds = (cap / kEncSuper * Tile::SB + 15) / 16 * 16 + cap * 4 + 16;
+  // four point tiles per wave where that still gives every CU two workgroups,
+  // else one; never more workgroups than two per CU (more would only repeat
+  // the codebook staging)
+  const int64_t slots = 2 * (int64_t)dev.num_cus;
+  auto groups_of = [&](int fn) { return (P + (int64_t)kEncWaves * fn * 32 - 1) / ((int64_t)kEncWaves * fn * 32); };
+  const bool wide = groups_of(4) >= slots;
+  const int64_t groups = groups_of(wide ? 4 : 1);
+  const int64_t blocks = groups < slots ? groups : slots;
   auto go = [&](auto kern) {
     hipError_t e = prepare_kernel(kern);
     if (e != hipSuccess) return e;
-    return launch_kernel(kern, dim3((unsigned)blocks), dim3(kEncThreads), lds, stream, w, P, d, cb, C, assign, sums,
-                         counts);
+    return launch_kernel(kern, dim3((unsigned)blocks), dim3(kEncThreads), lds, stream, w, P, d, cb, C, assign);
   };
-  if (!accum) return go(k_enc_assign<D, false, false>);
-  return agg ? go(k_enc_assign<D, true, true>) : go(k_enc_assign<D, true, false>);
+  if (!one) return wide ? go(k_enc_assign<DP, 4, 1, false>) : go(k_enc_assign<DP, 1, 1, false>);
+  if (C <= kEncFineMax) return wide ? go(k_enc_assign<DP, 4, 2, true>) : go(k_enc_assign<DP, 1, 2, true>);
+  return wide ? go(k_enc_assign<DP, 4, 1, true>) : go(k_enc_assign<DP, 1, 1, true>);
 }
 
+hipError_t launch_sum(const half_t* w, int64_t P, int d, int C, const uint32_t* assign, int64_t* sums,
+                      int64_t* counts, const DeviceInfo& dev, hipStream_t stream) {
+  const int per = 8 * d + 4;                 // table bytes per cluster
+  int cap = kEncSumBytes / per;              // clusters per table
+  int ranges = 1, copies = 1;
+  if (cap >= C) {
+    copies = cap / C < kEncSumThreads / kWave ? cap / C : kEncSumThreads / kWave;
+    cap = C;
+  } else {
+    ranges = (C + cap - 1) / cap;
+    cap = (C + ranges - 1) / ranges;
+    if (ranges > kEncSumMaxRanges) ranges = 1, cap = 0;
+  }
+  // tables: about one workgroup per CU in all, each with at least a table's
+  // worth of points; without tables enough threads to fill the chip
+  const int64_t per_wg = cap > 0 && copies == 1 ? 4 * (int64_t)cap : 4 * kEncSumThreads;
+  int64_t blocks = (P + per_wg - 1) / per_wg;
+  const int64_t most = (cap > 0 ? 1 : 2) * (int64_t)dev.num_cus / ranges;
+  if (blocks > most) blocks = most;
+  if (blocks < 1) blocks = 1;
+  const int lds = copies * cap * per;
+  unsigned long long* s = reinterpret_cast<unsigned long long*>(sums);
+  unsigned long long* c = reinterpret_cast<unsigned long long*>(counts);
+  auto go = [&](auto kern) {
+    hipError_t e = prepare_kernel(kern);
+    if (e != hipSuccess) return e;
+    return launch_kernel(kern, dim3((unsigned)blocks, (unsigned)ranges), dim3(kEncSumThreads), lds, stream, w, P, d, C,
+                         cap, copies, assign, s, c);
+  };
+  const uintptr_t at = reinterpret_cast<uintptr_t>(w);
+  if (d == 2 && at % 4 == 0) return go(k_enc_sum<2>);
+  if (d == 4 && at % 8 == 0) return go(k_enc_sum<4>);
+  if (d == 8 && at % 16 == 0) return go(k_enc_sum<8>);
+  return go(k_enc_sum<0>);
+}
+
+// Assignment of every point, and with accum the cluster sums and counts.
 hipError_t launch_assign(const half_t* w, int64_t P, int d, const half_t* cb, int C, uint32_t* assign, int64_t* sums,
                          int64_t* counts, bool accum, const DeviceInfo& dev, hipStream_t stream) {
-  switch (d) {
-    case 1: return launch_assign_d<1>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
-    case 2: return launch_assign_d<2>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
-    case 4: return launch_assign_d<4>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
-    case 8: return launch_assign_d<8>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
-    default: return launch_assign_d<0>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
+  if (C <= kEncDirectMax) {
+    if (d <= 2) return launch_direct<2>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
+    if (d <= 4) return launch_direct<4>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
+    if (d <= 8) return launch_direct<8>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
+    return launch_direct<16>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
   }
+  hipError_t e;
+  if (d <= 2) e = launch_assign_dp<2>(w, P, d, cb, C, assign, dev, stream);
+  else if (d <= 4) e = launch_assign_dp<4>(w, P, d, cb, C, assign, dev, stream);
+  else if (d <= 8) e = launch_assign_dp<8>(w, P, d, cb, C, assign, dev, stream);
+  else e = launch_assign_dp<16>(w, P, d, cb, C, assign, dev, stream);
+  if (e != hipSuccess || !accum) return e;
+  return launch_sum(w, P, d, C, assign, sums, counts, dev, stream);
 }
 
 }  // namespace
@@ -282,12 +683,14 @@ hipError_t launch_encode(const EncodeProblem& e, const DeviceInfo& dev, hipStrea
                         static_cast<const uint16_t*>(e.init), cb, cbn);
     if (err != hipSuccess) return err;
   }
-  for (int it = 0; it < e.iters; ++it) {
+  if (e.iters > 0) {
     err = launch_kernel(k_enc_zero, dim3(grid_for(cbn + C, 256)), dim3(256), 0, stream, sums, cbn + C);
     if (err != hipSuccess) return err;
+  }
+  for (int it = 0; it < e.iters; ++it) {
     err = launch_assign(w, P, d, reinterpret_cast<const half_t*>(cb), C, assign, sums, counts, true, dev, stream);
     if (err != hipSuccess) return err;
-    err = launch_kernel(k_enc_update, dim3(grid_for(cbn, 256)), dim3(256), 0, stream, cb, sums, counts, C, d);
+    err = launch_kernel(k_enc_update, dim3(grid_for(C, 64)), dim3(64), 0, stream, cb, sums, counts, C, d);
     if (err != hipSuccess) return err;
   }
   err = launch_assign(w, P, d, reinterpret_cast<const half_t*>(cb), C, assign, sums, counts, false, dev, stream);

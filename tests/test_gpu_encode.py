@@ -65,6 +65,80 @@ def test_encode_matches_oracle_bit_exact(case):
     check_encode(w, d, C, bits, init, iters, str(case))
 
 
+# The edges of the assignment paths: every distance up to 64 codewords, the
+# matrix cores beyond (blocks of 8 codewords per lane up to 512, of 16 after;
+# one LDS tile of the codebook up to 5376 codewords at d = 3 and 4, several
+# after), padded d, point counts that fill no tile, and cluster sums in one
+# LDS table, in ranges of clusters, and in global memory.
+EDGES = [
+    # N, K, d, C, bits, iters
+    (31, 64, 2, 64, 8, 2),
+    (31, 64, 2, 65, 8, 2),
+    (1, 300, 3, 100, 8, 2),         # fewer points than one workgroup takes
+    (257, 100, 5, 512, 12, 2),
+    (257, 100, 5, 513, 12, 2),
+    (100, 704, 11, 300, 12, 2),
+    (64, 512, 16, 257, 12, 2),
+    (300, 200, 1, 9000, 16, 2),
+    (120, 256, 4, 5376, 16, 2),
+    (120, 256, 4, 5377, 16, 2),
+    (700, 400, 4, 60000, 16, 1),    # more clusters than the LDS tables take
+    (1100, 1024, 2, 256, 8, 1),     # four point tiles per wave
+]
+
+
+@pytest.mark.parametrize("case", EDGES)
+def test_encode_path_edges_match_oracle_bit_exact(case):
+    N, K, d, C, bits, iters = case
+    print(f"[case] encode edge {case}", flush=True)
+    rng = np.random.default_rng(100 + sum(case))
+    w = pi.draw_weights(rng, N, K)
+    points = N * K // d
+    # more codewords than points: the rest are drawn
+    init = pi.subvectors_at(w, d, pi.init_point_ids(rng, points, min(C, points)))
+    init = np.concatenate([init, pi.draw_codebook(rng, C - len(init), d)]) if len(init) < C else init
+    check_encode(w, d, C, bits, np.ascontiguousarray(init), iters, str(case))
+
+
+@pytest.mark.parametrize("d,C,bits", [(1, 300, 12), (2, 256, 8), (3, 1000, 12), (4, 4096, 12), (4, 6000, 16), (8, 600, 12)])
+@pytest.mark.parametrize("values", ["lattice", "sparse", "alike", "subnormal"])
+def test_encode_ties_go_to_the_lowest_index(values, d, C, bits):
+    """Exact ties between codewords of different blocks and tiles: values on a
+    coarse lattice, mostly zero weights with repeated codewords, all codewords
+    alike, and fp16 subnormals (whose distances differ by single units)."""
+    rng = np.random.default_rng(d * C + len(values))
+    N, K = 48, 24 * d
+    if values == "subnormal":
+        w = (rng.integers(-9, 10, (N, K)) * 2.0 ** -24).astype(np.float16)
+        init = (rng.integers(-9, 10, (C, d)) * 2.0 ** -24).astype(np.float16)
+    else:
+        w = (rng.integers(-3, 4, (N, K)) * 0.25).astype(np.float16)
+        if values == "sparse":
+            w[rng.random((N, K)) < 0.7] = 0
+        init = (rng.integers(-3, 4, (C, d)) * 0.25).astype(np.float16)
+        if values == "alike":
+            init[:] = np.float16(0.5)
+    check_encode(w, d, C, bits, init, 1, f"{values} d={d} C={C}")
+
+
+def test_encode_never_picks_a_non_finite_codeword():
+    """A codeword with an infinity or a NaN is at no finite distance; the
+    others are chosen as if it were not there."""
+    rng = np.random.default_rng(11)
+    d, bits = 4, 16
+    w = pi.draw_weights(rng, 64, 256)
+    for C in (50, 300, 6000):
+        init = pi.draw_codebook(rng, C, d)
+        bad = init.copy()
+        bad[::3, 0] = np.inf
+        bad[1::5, 3] = np.nan
+        bad[2::7, 1] = -np.inf
+        keep = np.isfinite(bad).all(1)
+        ids_ref = np.flatnonzero(keep)[enc.assign(w.reshape(-1, d), init[keep])]
+        _, idx = gpu_encode(w, d, bits, bad, 0)
+        assert np.array_equal(orc.unpack_indices(idx, 64, bits, C).reshape(-1), ids_ref), C
+
+
 def test_encode_is_deterministic_and_accepts_in_place_init():
     rng = np.random.default_rng(7)
     N, K, d, C, bits = 512, 1024, 2, 256, 8
