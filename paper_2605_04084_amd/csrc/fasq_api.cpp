@@ -147,7 +147,7 @@ fasq_status run(const Problem& p, Regime regime, hipStream_t stream, void* works
     }
     if (e == hipErrorNotSupported) e = launch_gemm_mfma(p, dev, stream, workspace, workspace_bytes);
   }
-  if (e == hipErrorNotSupported) e = launch_generic(p, stream);
+  if (e == hipErrorNotSupported) e = launch_generic(p, dev, stream);
   if (e != hipSuccess) return hip_fail("kernel launch", e);
   t_last_error.clear();
   return FASQ_OK;
@@ -344,7 +344,7 @@ fasq_status fasq_pq_gemv_ex(const void* x, int64_t M, int64_t K, int64_t N, cons
   if (e != hipSuccess) return fasq::hip_fail("querying the current device", e);
   e = hipErrorNotSupported;
   if (!fasq::force_generic()) e = fasq::launch_gemv_sub(p, workspace, workspace_bytes, dev, stream);
-  if (e == hipErrorNotSupported) e = fasq::launch_generic(p, stream);
+  if (e == hipErrorNotSupported) e = fasq::launch_generic(p, dev, stream);
   if (e != hipSuccess) return fasq::hip_fail("kernel launch", e);
   fasq::t_last_error.clear();
   return FASQ_OK;

@@ -43,7 +43,7 @@ hipError_t device_info(DeviceInfo* out);
 
 // Launchers.  Each returns hipSuccess or the launch error; none synchronizes.
 hipError_t launch_reconstruct(const Problem& p, void* w, hipStream_t stream);
-hipError_t launch_generic(const Problem& p, hipStream_t stream);
+hipError_t launch_generic(const Problem& p, const DeviceInfo& dev, hipStream_t stream);
 
 // Tuned decode kernel for M <= kGemvMaxTokens.  Returns hipErrorNotSupported
 // (without launching) when no tuned variant applies.
