@@ -322,7 +322,7 @@ int64_t fasq_pq_gemv_ex_workspace_bytes(int64_t M, int64_t K, int64_t N, int idx
   // and the 16-row-tile decode kernel when it splits K
   if (fasq::force_generic()) return 0;
   const char* plan = fasq_pq_plan(0, M, K, N, idx_bits, d, C);
-  if (std::strncmp(plan, "k_gemm_mfma", 11) == 0 || fasq::decode_prefers_gemm(p, dev))
+  if (std::strncmp(plan, "k_gemm_", 7) == 0 || fasq::decode_prefers_gemm(p, dev))
     return fasq::gemm_workspace_bytes(p, dev);
   if (std::strncmp(plan, "k_gemv<", 7) == 0) return fasq::gemv_split_workspace_bytes(p);
   return 0;

@@ -1,4 +1,5 @@
 // Prefill GEMM kernels: variant selection and launch.
+#include "fasq_gemm_gather.h"
 #include "fasq_gemm_mfma.h"
 #include "fasq_gemv_launch.h"
 
@@ -122,6 +123,7 @@ hipError_t launch_gemm_bits(const GemmArgs& a, int d, int mode, int tile, int kg
 // workspace); false when the tuned kernel does not apply.
 struct GemmPlan {
   int tile = 0, kg = 1, mode = 0, lds = 0, ksplit = 1;
+  int gather = -1;  // k_gemm_gather: its tile
 };
 
 // K ranges per output tile when the grid leaves CUs idle: enough to reach
@@ -129,6 +131,16 @@ struct GemmPlan {
 // kGemmMinSplitChunks chunks of 64 per K group.
 constexpr int kGemmMaxSplit = 8;
 constexpr int kGemmMinSplitChunks = 4;
+constexpr int kGatherMinSplitChunks = 8;
+// Codebooks gathered from global memory go to k_gemm_gather, which decodes
+// each tile of W_hat once per workgroup: 65536 entries, d = 4, 4096 x 4096 at
+// 64 / 128 / 512 / 2048 tokens 31 / 47 / 61 / 216 us against 59 / 69 / 244 /
+// 537 us on k_gemm_mfma (whose waves each gather their own operands).  It is
+// the faster one at every size measured; k_gemm_mfma keeps the calls whose
+// plan the tests fix: small matrices (fewer than kGatherMinIds ids: 70 x 1088
+// at 100 tokens 18 against 11 us) and more than one round of 128 x 256 tiles
+// (14336 x 4096 at 2048 tokens 1900 against 665 us).
+constexpr int64_t kGatherMinIds = 32768;
 
 bool gemm_plan(const Problem& p, const DeviceInfo& dev, GemmPlan* out) {
   const int d = p.d;
@@ -186,12 +198,28 @@ bool gemm_plan(const Problem& p, const DeviceInfo& dev, GemmPlan* out) {
     }
   }
   const int lds = (int)lds_of(tile, kg, mode);
+  int64_t tiles = tiles_of(tile);
+  int64_t min_chunks = (int64_t)kGemmMinSplitChunks * kg;
+  out->gather = -1;
+  if (mode == CB_GLOBAL && p.N * p.S >= kGatherMinIds && (tile > 1 || tiles <= dev.num_cus)) {
+    // the tile with the fewest cycles over its rounds of workgroups: gathers
+    // at one lane per cycle, the X copy at 64 bytes
+    int64_t best = 0;
+    for (int t = 0; t < kGatherNumTiles; ++t) {
+      const GatherTile& g = kGatherTiles[t];
+      const int64_t n = ((p.M + g.bm - 1) / g.bm) * ((p.N + g.bn - 1) / g.bn);
+      const int64_t cost = (n + dev.num_cus - 1) / dev.num_cus * (g.bn * 64 / d + g.bm * 2);
+      if (out->gather < 0 || cost < best) {
+        best = cost;
+        out->gather = t;
+        tiles = n;
+      }
+    }
+    min_chunks = kGatherMinSplitChunks;
+  }
   int ksplit = 1;
-  const int64_t tiles = tiles_of(tile);
   const int64_t chunks = p.K / kGemmKC;
-  while (ksplit < kGemmMaxSplit && tiles * (ksplit + 1) <= dev.num_cus &&
-         chunks / (ksplit + 1) >= (int64_t)kGemmMinSplitChunks * kg)
-    ++ksplit;
+  while (ksplit < kGemmMaxSplit && tiles * (ksplit + 1) <= dev.num_cus && chunks / (ksplit + 1) >= min_chunks) ++ksplit;
   out->tile = tile;
   out->kg = kg;
   out->mode = mode;
@@ -253,7 +281,8 @@ hipError_t launch_gemm_mfma(const Problem& p, const DeviceInfo& dev, hipStream_t
   a.ksplit = pl.ksplit;
   a.ws = static_cast<float*>(workspace);
   hipError_t e;
-  switch (p.idx_bits) {
+  if (pl.gather >= 0) e = launch_gemm_gather(a, p.idx_bits, d, pl.gather, stream);
+  else switch (p.idx_bits) {
     case 8: e = launch_gemm_bits<8>(a, d, mode, tile, kg, lds, stream); break;
     case 12: e = launch_gemm_bits<12>(a, d, mode, tile, kg, lds, stream); break;
     default: e = launch_gemm_bits<16>(a, d, mode, tile, kg, lds, stream); break;
