@@ -248,19 +248,48 @@ def reconstruct_raw(idx, N, K, idx_bits, d, codebook, C, w, stream=0) -> int:
 # Torch-tensor entry points
 # ---------------------------------------------------------------------------
 
+# A call's host time is most of what a small layer costs (4096 x 1024, one
+# token: 3.7 us on the GPU, 11 us a call in the binding with torch's stream object,
+# its device context and an import per call, 7.5 us without), so the tensor
+# entry points below ask torch for plain integers: the raw stream handle of
+# the tensor's device, and a device switch only when another device is current.
+_torch_module = None
+
+
 def _torch():
-    import torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
 
-    return torch
+        _torch_module = torch
+    return _torch_module
 
 
-def _stream_handle(tensor) -> int:
+def _stream_of(device: int) -> int:
+    """The handle of torch's current stream on the device of that index."""
+    return _torch()._C._cuda_getCurrentRawStream(device)
+
+
+def _on_device(device: int, fn, *args) -> int:
+    """``fn(*args, stream)`` with that device current."""
     torch = _torch()
-    return torch.cuda.current_stream(tensor.device).cuda_stream
+    if torch.cuda.current_device() == device:
+        return fn(*args, _stream_of(device))
+    with torch.cuda.device(device):
+        return fn(*args, _stream_of(device))
+
+
+def _row_bytes(K: int, d: int, idx_bits: int) -> int:
+    """``fasq_idx_row_bytes`` of sizes taken from tensors (-1 when invalid)."""
+    if K < 1 or d < 1 or K % d or idx_bits not in (8, 12, 16):
+        return -1
+    return (K // d * idx_bits + 7) // 8
 
 
 def _require(t, name, dtype, ndim):
     torch = _torch()
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.dim() == ndim and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if not t.is_cuda:
@@ -283,23 +312,22 @@ def _matmul(fn, x, idx, idx_bits, d, codebook, out=None):
     C, dd = codebook.shape
     if dd != d:
         raise ValueError(f"codebook is [C x {dd}] but d = {d}")
-    want = idx_row_bytes(K, d, idx_bits)
+    want = _row_bytes(K, d, idx_bits)
     if want < 0:
         raise ValueError("invalid (K, d, idx_bits)")
     if R != want:
         raise ValueError(f"idx rows are {R} bytes, expected {want}")
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=x.device)
+        out = x.new_empty((M, N))
     else:
         _require(out, "out", torch.float16, 2)
         if tuple(out.shape) != (M, N):
             raise ValueError("out must be [M x N]")
-    for t in (idx, codebook, out):
-        if t.device != x.device:
-            raise ValueError("all tensors must be on one device")
-    with torch.cuda.device(x.device):
-        _check(fn(x.data_ptr(), M, K, N, idx.data_ptr(), idx_bits, d, codebook.data_ptr(), C,
-                  out.data_ptr(), _stream_handle(x)))
+    device = x.get_device()
+    if idx.get_device() != device or codebook.get_device() != device or out.get_device() != device:
+        raise ValueError("all tensors must be on one device")
+    _check(_on_device(device, fn, x.data_ptr(), M, K, N, idx.data_ptr(), idx_bits, d, codebook.data_ptr(), C,
+                      out.data_ptr()))
     return out
 
 
@@ -331,9 +359,10 @@ def pq_gemv_batched(x, idxs, idx_bits: int, d: int, codebooks, outs=None):
     M, K = x.shape
     if len(idxs) != len(codebooks) or (outs is not None and len(outs) != len(idxs)):
         raise ValueError("idxs, codebooks and outs must have equal lengths")
-    want = idx_row_bytes(K, d, idx_bits)
+    want = _row_bytes(K, d, idx_bits)
     if want < 0:
         raise ValueError("invalid (K, d, idx_bits)")
+    device = x.get_device()
     ys = []
     for i, (idx, cb) in enumerate(zip(idxs, codebooks)):
         _require(idx, f"idx[{i}]", torch.uint8, 2)
@@ -343,20 +372,19 @@ def pq_gemv_batched(x, idxs, idx_bits: int, d: int, codebooks, outs=None):
         if idx.shape[1] != want:
             raise ValueError(f"idx[{i}] rows are {idx.shape[1]} bytes, expected {want}")
         if outs is None:
-            y = torch.empty((M, idx.shape[0]), dtype=torch.float16, device=x.device)
+            y = x.new_empty((M, idx.shape[0]))
         else:
             y = outs[i]
             _require(y, f"out[{i}]", torch.float16, 2)
             if tuple(y.shape) != (M, idx.shape[0]):
                 raise ValueError(f"out[{i}] must be [M x N]")
         for t in (idx, cb, y):
-            if t.device != x.device:
+            if t.get_device() != device:
                 raise ValueError("all tensors must be on one device")
         ys.append(y)
-    with torch.cuda.device(x.device):
-        _check(gemv_batched_raw(x.data_ptr(), M, K, [t.data_ptr() for t in idxs], [t.shape[0] for t in idxs],
-                                [t.data_ptr() for t in codebooks], [t.shape[0] for t in codebooks],
-                                [t.data_ptr() for t in ys], idx_bits, d, _stream_handle(x)))
+    _check(_on_device(device, gemv_batched_raw, x.data_ptr(), M, K, [t.data_ptr() for t in idxs],
+                      [t.shape[0] for t in idxs], [t.data_ptr() for t in codebooks], [t.shape[0] for t in codebooks],
+                      [t.data_ptr() for t in ys], idx_bits, d))
     return ys
 
 
@@ -378,9 +406,8 @@ def pq_reconstruct(idx, K: int, idx_bits: int, d: int, codebook, out=None):
         _require(out, "out", torch.float16, 2)
         if tuple(out.shape) != (N, K):
             raise ValueError("out must be [N x K]")
-    with torch.cuda.device(idx.device):
-        _check(lib().fasq_pq_reconstruct(idx.data_ptr(), N, K, idx_bits, d, codebook.data_ptr(), C,
-                                         out.data_ptr(), _stream_handle(idx)))
+    _check(_on_device(idx.get_device(), lib().fasq_pq_reconstruct, idx.data_ptr(), N, K, idx_bits, d,
+                      codebook.data_ptr(), C, out.data_ptr()))
     return out
 
 
@@ -419,10 +446,9 @@ def pq_encode(w, d: int, idx_bits: int, init_codebook, iters: int, workspace=Non
         raise ValueError("all tensors must be on one device")
     codebook = torch.empty((C, d), dtype=torch.float16, device=w.device)
     idx = torch.empty((N, R), dtype=torch.uint8, device=w.device)
-    with torch.cuda.device(w.device):
-        _check(encode_raw(w.data_ptr(), N, K, d, C, idx_bits, init_codebook.data_ptr(), iters, codebook.data_ptr(),
-                          idx.data_ptr(), workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                          _stream_handle(w)))
+    _check(_on_device(w.get_device(), encode_raw, w.data_ptr(), N, K, d, C, idx_bits, init_codebook.data_ptr(), iters,
+                      codebook.data_ptr(), idx.data_ptr(), workspace.data_ptr(),
+                      workspace.numel() * workspace.element_size()))
     return codebook, idx
 
 
@@ -464,11 +490,11 @@ def pq_gemv_ex(x, idx, idx_bits: int, d: int, codebook, out=None, workspace=None
         stride = C * d
     else:
         stride = 0
-    want = idx_row_bytes(K, d, idx_bits)
+    want = _row_bytes(K, d, idx_bits)
     if want < 0 or R != want:
         raise ValueError(f"idx rows are {R} bytes, expected {want}")
     if out is None:
-        out = torch.empty((M, N), dtype=torch.float16, device=x.device)
+        out = x.new_empty((M, N))
     else:
         _require(out, "out", torch.float16, 2)
         if tuple(out.shape) != (M, N):
@@ -480,12 +506,11 @@ def pq_gemv_ex(x, idx, idx_bits: int, d: int, codebook, out=None, workspace=None
         workspace = torch.empty(need, dtype=torch.uint8, device=x.device)
     ws_ptr = workspace.data_ptr() if workspace is not None else 0
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    for t in (idx, codebook, out):
-        if t.device != x.device:
-            raise ValueError("all tensors must be on one device")
-    with torch.cuda.device(x.device):
-        _check(gemv_ex_raw(x.data_ptr(), M, K, N, idx.data_ptr(), idx_bits, d, codebook.data_ptr(), C, stride,
-                           out.data_ptr(), ws_ptr, ws_bytes, _stream_handle(x)))
+    device = x.get_device()
+    if idx.get_device() != device or codebook.get_device() != device or out.get_device() != device:
+        raise ValueError("all tensors must be on one device")
+    _check(_on_device(device, gemv_ex_raw, x.data_ptr(), M, K, N, idx.data_ptr(), idx_bits, d, codebook.data_ptr(), C,
+                      stride, out.data_ptr(), ws_ptr, ws_bytes))
     return out
 
 
@@ -561,7 +586,7 @@ class LaunchList:
         """Queue the recorded launches on ``stream`` (an integer HIP stream
         handle, a torch stream, or None for torch's current stream)."""
         if stream is None:
-            stream = _torch().cuda.current_stream().cuda_stream
+            stream = _stream_of(_torch().cuda.current_device())
         elif not isinstance(stream, int):
             stream = stream.cuda_stream
         _check(lib().fasq_launch_list_run(self._live(), stream))
