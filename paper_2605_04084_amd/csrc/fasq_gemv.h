@@ -69,10 +69,9 @@ struct GemvArgs {
   int seg_slabs;
   float* ws;
   int64_t ld_ws;
-  // 1 (K split with one slab per segment and many tokens, or a codebook head
-  // in LDS): the partials of each round of tiles (tile j of every row group)
-  // are summed and written as soon as the round is done, so LDS holds one
-  // round's partials instead of every tile's
+  // Above 0 the partials of each round of round_sum tiles per row group are
+  // summed and written as soon as the round is done, so LDS holds one round's
+  // partials instead of every tile's
   int round_sum;
   GemvPart part[kGemvMaxParts];
 };
@@ -107,7 +106,9 @@ constexpr int kXSlabBatch = 4;       // x words (16 B) in flight per thread when
 // operands are zeroed.  SLAB: x is staged in slabs (always with MASK); the
 // slab loop keeps more state live, so these variants run a shallower
 // pipeline (kGemvSlabPipe loads) to stay within the registers of 16 waves.
-template <int BITS, int D, int T, int MODE, int MR, bool MASK, bool SLAB>
+// RND (not with SLAB): rounds of tiles (GemvArgs::round_sum), and K split over
+// gridDim.z segments of CHS chunk columns with x in registers.
+template <int BITS, int D, int T, int MODE, int MR, bool MASK, bool SLAB, bool RND>
 __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   constexpr int G = Chunk<BITS>::G;      // ids per chunk
   constexpr int DW = Chunk<BITS>::DW;    // dwords per chunk
@@ -118,6 +119,7 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   static_assert(L % T == 0, "pipeline depth must be a multiple of T");
   static_assert(MR == 16, "16 token slots");
   static_assert(!SLAB || MASK, "slabs take the column checks");
+  static_assert(!RND || (!SLAB && !MASK), "rounds outside slabs take whole rows");
 
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   uint8_t* xl = smem + a.cb_bytes;
@@ -149,6 +151,8 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   // Units past the end of this wave's work, and rows past N, load the first
   // chunk of the table (one address for the whole wave: a single request) so
   // that every iteration issues exactly one load and the waits stay exact.
+  // (Buffer loads past the table's end instead, which touch no memory,
+  // measured up to 9 % slower.)
   // Byte offsets into the index table are 32-bit (the host checks that the
   // table is below 4 GiB) from one uniform base.
   auto tile_of = [&](int rt) { return (int64_t)blockIdx.x + (int64_t)(rt * Q + q) * gridDim.x; };
@@ -158,7 +162,7 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   // the slabs of this workgroup's K segment: [sb0, sb1)
   const int sb0 = SLAB ? (int)blockIdx.z * a.seg_slabs : 0;
   const int sb1 = SLAB ? (sb0 + a.seg_slabs < a.nslab ? sb0 + a.seg_slabs : a.nslab) : 1;
-  int c0 = sb0 * a.CHS, chs = CH;  // the slab: chunk columns [c0, c0 + chs)
+  int c0 = RND ? (int)blockIdx.z * a.CHS : sb0 * a.CHS, chs = CH;  // the slab: chunk columns [c0, c0 + chs)
   // byte offset of the lane's chunk in column t of the slab within its row,
   // or ~0 for columns past the slab (set per slab)
   uint32_t col_off[T];
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
       const half_t* xg = a.x + (int64_t)mrow * a.K;
 #pragma unroll
       for (int t = 0; t < T; ++t) {
-        const int c = ccol_raw(t) < CH ? ccol_raw(t) : CH - 1;
+        const int c = RND ? c0 + ccol_raw(t) : ccol_raw(t) < CH ? ccol_raw(t) : CH - 1;
 #pragma unroll
         for (int s = 0; s < SPC; ++s) xreg[t * SPC + s] = *reinterpret_cast<const half8_t*>(xg + c * (G * D) + s * 8);
       }
@@ -258,7 +262,8 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
     __syncthreads();
   }
 
-  const bool rounds = (SLAB || MODE == CB_SPLIT) && a.round_sum != 0;
+  const bool rounds = (SLAB || MODE == CB_SPLIT || RND) && a.round_sum != 0;
+  const int RT = RND ? a.round_sum : 1;  // tiles of a round per row group
   // fixed-order sum over the P waves of the partials of the workgroup's
   // local rows [r0, r0 + nr) (LDS rows from lr0), one fp16 rounding, or one
   // fp32 partial of this K segment; consecutive threads take consecutive
@@ -274,7 +279,7 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
         float sum = 0.f;
         const float* pr = red + ((lr0 + rr) * M + m) * PS;
         for (int pp = 0; pp < P; ++pp) sum += pr[pp];
-        if (SLAB && gridDim.z > 1) a.ws[((int64_t)blockIdx.z * M + m) * a.ld_ws + pt.ws_row + n] = sum;
+        if ((SLAB || RND) && gridDim.z > 1) a.ws[((int64_t)blockIdx.z * M + m) * a.ld_ws + pt.ws_row + n] = sum;
         else pt.y[(int64_t)m * pt.ldy + n] = static_cast<half_t>(sum);
       }
     }
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
           if (t == T - 1) {
             // lane l holds rows m = 4g .. 4g + 3 of column nl of the 16 x 16
             // tile; the slabs of a row are summed in slab order by this lane
-            const int lrow = ((rounds ? 0 : u / T) * Q + q) * 16 + nl;
+            const int lrow = ((rounds ? (RND ? u / T % RT : 0) : u / T) * Q + q) * 16 + nl;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
               const int m = 4 * g + k;
@@ -355,9 +360,10 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
         // a round of tiles done (the condition is the same in every wave:
         // all waves have the same units): sum it while the next round's
         // loads are in flight
-        if (rounds && t == T - 1 && u < nunits) {
+        if (rounds && t == T - 1 && u < nunits && (!RND || u / T % RT == RT - 1 || u / T == nrt - 1)) {
+          const int first = RND ? u / T / RT * RT : u / T;  // first tile of the round
           __syncthreads();
-          sum_rows((u / T) * Q * 16, 0, Q * 16);
+          sum_rows(first * Q * 16, 0, (u / T + 1 - first) * Q * 16);
           __syncthreads();
         }
       }

@@ -73,7 +73,7 @@ hipError_t launch_gemv_variant(const GemvArgs& a, bool mask, int threads, dim3 b
   if (a.nslab > 1) {  // x in slabs (T up to 4): the plan name carries a trailing 1
     if constexpr (T <= 4) {
       if (plan_record("k_gemv", {BITS, D, T, MODE, MR, 1, 1})) return hipSuccess;
-      auto kern = k_gemv<BITS, D, T, MODE, MR, true, true>;
+      auto kern = k_gemv<BITS, D, T, MODE, MR, true, true, false>;
       hipError_t e = prepare_kernel(kern);
       if (e != hipSuccess) return e;
       return launch_kernel(kern, blocks, dim3(threads), lds, stream, a);
@@ -81,7 +81,18 @@ hipError_t launch_gemv_variant(const GemvArgs& a, bool mask, int threads, dim3 b
       return hipErrorNotSupported;
     }
   }
-  auto kern = mask ? k_gemv<BITS, D, T, MODE, MR, true, false> : k_gemv<BITS, D, T, MODE, MR, false, false>;
+  if ((MODE == CB_REPL || MODE == CB_LDS) && a.round_sum > 0) {  // rounds or K segments with x in registers: a trailing 0, 1
+    if constexpr (T * Chunk<BITS>::G * D / 8 <= 8) {
+      if (plan_record("k_gemv", {BITS, D, T, MODE, MR, 0, 0, 1})) return hipSuccess;
+      auto kern = k_gemv<BITS, D, T, MODE, MR, false, false, true>;
+      hipError_t e = prepare_kernel(kern);
+      if (e != hipSuccess) return e;
+      return launch_kernel(kern, blocks, dim3(threads), lds, stream, a);
+    } else {
+      return hipErrorNotSupported;
+    }
+  }
+  auto kern = mask ? k_gemv<BITS, D, T, MODE, MR, true, false, false> : k_gemv<BITS, D, T, MODE, MR, false, false, false>;
   if (plan_record("k_gemv", {BITS, D, T, MODE, MR, mask ? 1 : 0})) return hipSuccess;
   hipError_t e = prepare_kernel(kern);
   if (e != hipSuccess) return e;
@@ -170,8 +181,9 @@ constexpr int kRoundSumFromTokens = 11;
 constexpr int kRoundHeadFromTokens = 4;
 
 struct GemvSplit {
-  int nseg = 1;      // K segments (1: no split)
-  int64_t chs = 0;   // chunk columns per segment
+  int nseg = 1;       // K segments (1: no split)
+  int64_t chs = 0;    // chunk columns per segment
+  bool regs = false;  // each segment's x in registers
 };
 
 inline GemvSplit gemv_split_plan(const Problem& p) {
@@ -183,6 +195,21 @@ inline GemvSplit gemv_split_plan(const Problem& p) {
   const int64_t XCB = (int64_t)G * p.d * 2;
   const int64_t x_total = p.M * CH * XCB;
   if (x_total <= kXSegBytes) return sp;
+  // segments whose x fits the waves' registers, where the codebook is in LDS:
+  // no x staging at all.  down_proj 4096 x 14336 (d = 2, C = 256) at 4 / 8 /
+  // 16 tokens
+  // 14.0 / 14.6 / 17.1 us, against 14.7 / 15.3 us with each segment's x in LDS
+  // and 25.8 us on the K-split GEMM.
+  const int mode = choose_cb_mode(p.C, p.d);
+  if (mode == CB_REPL || mode == CB_LDS) {
+    for (int n = 2; n <= kGemvMaxSegs; n *= 2) {
+      if (CH % n || !gemv_x_in_regs(CH / n, G, p.d) || (int64_t)n * p.M * p.N * 4 > kGemvSplitMaxWs) continue;
+      sp.nseg = n;
+      sp.chs = CH / n;
+      sp.regs = true;
+      return sp;
+    }
+  }
   int ks = 2;
   while (ks < kGemvMaxSegs && x_total / ks > kXSegBytes) ks *= 2;
   const int64_t chs = ((CH + ks - 1) / ks + 3) / 4 * 4;
@@ -254,16 +281,19 @@ hipError_t launch_gemv_bits(const Problem* ps, int count, const DeviceInfo& dev,
 
   const int XCB = G * d * 2;  // bytes of x per chunk column and token
   // x in registers (whole rows, no masked columns) needs no LDS
-  const bool x_in_regs = gemv_x_in_regs(CH, G, d);
+  bool x_in_regs = gemv_x_in_regs(CH, G, d);
   int64_t CHS = CH;  // chunk columns per x slab
   // K split over workgroups with a caller workspace (one matrix): each
   // segment is one slab
   int nseg = 1;
+  bool seg_regs = false;
   if (count == 1 && p.ws != nullptr && !(reinterpret_cast<uintptr_t>(p.ws) & 3)) {
     const GemvSplit sp = gemv_split_plan(p);
     if (sp.nseg > 1 && p.ws_bytes >= (int64_t)sp.nseg * p.M * p.N * 4) {
       nseg = sp.nseg;
       CHS = sp.chs;
+      seg_regs = sp.regs;
+      x_in_regs = x_in_regs || seg_regs;
     }
   }
   if (nseg == 1 && !x_in_regs && p.M * (CH * XCB + 16) > kXWholeBytes) {
@@ -273,7 +303,7 @@ hipError_t launch_gemv_bits(const Problem* ps, int count, const DeviceInfo& dev,
     const int64_t ns = (CH + cmax - 1) / cmax;
     CHS = ((CH + ns - 1) / ns + 3) / 4 * 4;  // near-equal slabs, whole K groups
   }
-  const int nslab = (int)((CH + CHS - 1) / CHS);
+  const int nslab = seg_regs ? 1 : (int)((CH + CHS - 1) / CHS);
   const int T = gemv_pick_t(CHS);
   if (T == 0) return hipErrorNotSupported;
   const int P = (int)(((CHS + 3) / 4 + T - 1) / T);
@@ -342,16 +372,29 @@ hipError_t launch_gemv_bits(const Problem* ps, int count, const DeviceInfo& dev,
   int64_t tw = (ntiles + nwg - 1) / nwg;
   tw = (tw + Q - 1) / Q * Q;
   // summing by rounds, LDS holds one round of Q tiles' partials at a time
-  const bool rounds = (nseg > 1 && p.M >= kRoundSumFromTokens) || (mode == CB_SPLIT && p.M >= kRoundHeadFromTokens);
+  const bool rounds = (nseg > 1 && !seg_regs && p.M >= kRoundSumFromTokens) ||
+                      (mode == CB_SPLIT && p.M >= kRoundHeadFromTokens);
   const int64_t tw_max = rounds ? (avail >= Q * 16 * p.M * PS * 4 ? tw : 0)
                                 : avail / (16 * p.M * PS * 4) / Q * Q;
   if (tw_max < Q) return hipErrorNotSupported;
-  if (tw > tw_max) {
+  // With x in registers and the codebook in LDS, a workgroup whose tiles'
+  // partials do not all fit works in rounds of as many as do (of equal size),
+  // so that the call stays one round of workgroups: a second one costs a
+  // staging of x and the codebook (about 8 us of the first tile's 10).
+  // gate+up (2 x 14336 x 4096, d = 2, C = 256) at 16 tokens: 23.3
+  // against 33.4 us in two rounds of workgroups.
+  const bool whole = x_in_regs && nslab == 1 && (mode == CB_REPL || mode == CB_LDS);
+  int64_t round_tiles = tw;  // tiles whose partials are in LDS at a time
+  if (whole && tw > tw_max) {
+    const int64_t n = tw / Q, per = tw_max / Q, nr = (n + per - 1) / per;
+    round_tiles = (n + nr - 1) / nr * Q;
+  } else if (tw > tw_max) {
     tw = tw_max;
     nwg = (ntiles + tw - 1) / tw;
   }
   if (nwg > 0x7fffffff || tw * 16 > 0x7fffffff) return hipErrorNotSupported;
-  const int lds = (int)(cb_bytes + x_bytes + (rounds ? Q : tw) * 16 * p.M * PS * 4);
+  if (round_tiles > tw) round_tiles = tw;
+  const int lds = (int)(cb_bytes + x_bytes + (rounds ? Q : round_tiles) * 16 * p.M * PS * 4);
 
   GemvArgs a = {};
   a.x = static_cast<const half_t*>(p.x);
@@ -371,7 +414,7 @@ hipError_t launch_gemv_bits(const Problem* ps, int count, const DeviceInfo& dev,
   a.seg_slabs = nseg > 1 ? 1 : nslab;
   a.ws = nseg > 1 ? static_cast<float*>(p.ws) : nullptr;
   a.ld_ws = p.N;
-  a.round_sum = rounds ? 1 : 0;
+  a.round_sum = rounds ? 1 : whole && (round_tiles < tw || nseg > 1) ? (int)(round_tiles / Q) : 0;
   int k = 0;
   for (int i = 0; i < count; ++i) {
     const int64_t base = tiles_of[i] / cuts[i], extra = tiles_of[i] % cuts[i];
