@@ -16,10 +16,10 @@
 //     (split-K inside the workgroup); each wave covers T chunk columns per
 //     lane.  Partials go to LDS and are summed over the P waves in a fixed
 //     order after one barrier: deterministic, no atomics, no workspace.
-//   * Every wave runs a software pipeline that keeps kGemvPipe - 1 chunk
-//     loads in flight, so the index stream keeps HBM busy while earlier
-//     chunks are decoded.  Loads are unconditional (clamped addresses) so
-//     the compiler can count outstanding loads exactly.
+//   * Every wave runs a software pipeline that keeps kGemvWindow chunk loads
+//     in flight, so the index stream keeps HBM busy while earlier chunks are
+//     decoded.  Loads are unconditional, with code of its own for the last
+//     units, so the compiler can count outstanding loads exactly.
 //   * The codebook (replicated per lane slot when small) and x are staged in
 //     LDS once per workgroup before any index load is issued: the vector L1
 //     returns data in order, so L2-resident loads queued behind HBM loads
@@ -83,7 +83,11 @@ constexpr int kGemvPipe = 8;      // load units per wave in the software pipelin
 // lanes of a wave that write one MFMA result (16 rows x 4 tokens) hit one
 // or two banks when M is even, and the final sum's reads hit one.
 __host__ __device__ constexpr int gemv_red_stride(int P) { return P > 1 ? P + 1 : 1; }
-constexpr int kGemvSlabPipe = 4;  // the same with x in slabs
+// Index loads each wave of the 16-row-tile kernel keeps in flight (see
+// kM1Window), none of them past its last unit.  With seven, the units past
+// the end loading one address, o_proj (4096 x 4096, d = 2, C = 256) took 1.7 us
+// longer: the waves end only when those loads are back.
+constexpr int kGemvWindow = 2;
 // Index loads each single-token wave keeps in flight.  Two per wave (32 KB
 // per CU at 16 waves) already saturate a CU's share of HBM; more only make
 // waves wait at the issue of loads that cannot enter the queue, where they
@@ -115,8 +119,9 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   constexpr int CBY = DW * 4;            // chunk bytes
   constexpr int SPC = G * D / 8;         // MFMA steps (8 K values each) per chunk
   constexpr int XCB = G * D * 2;         // bytes of x per chunk column and token
-  constexpr int L = SLAB ? (T > kGemvSlabPipe ? T : kGemvSlabPipe) : kGemvPipe;
-  static_assert(L % T == 0, "pipeline depth must be a multiple of T");
+  constexpr int L = T > 4 ? T : 4;       // load slots, units per unrolled group
+  constexpr int W = kGemvWindow;         // index loads in flight per wave
+  static_assert(L % T == 0 && W < L, "load slots must cover the window and whole tiles");
   static_assert(MR == 16, "16 token slots");
   static_assert(!SLAB || MASK, "slabs take the column checks");
   static_assert(!RND || (!SLAB && !MASK), "rounds outside slabs take whole rows");
@@ -148,14 +153,17 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   const int CH = (int)a.CH;
   auto ccol_raw = [&](int t) { return (p * T + t) * 4 + g; };
 
-  // Units past the end of this wave's work, and rows past N, load the first
-  // chunk of the table (one address for the whole wave: a single request) so
-  // that every iteration issues exactly one load and the waits stay exact.
-  // (Buffer loads past the table's end instead, which touch no memory,
-  // measured up to 9 % slower.)
+  // Rows past N (and the early loads of a wave without that many units) load
+  // the first chunk of the table, one address for the whole wave.
   // Byte offsets into the index table are 32-bit (the host checks that the
   // table is below 4 GiB) from one uniform base.
   auto tile_of = [&](int rt) { return (int64_t)blockIdx.x + (int64_t)(rt * Q + q) * gridDim.x; };
+  // (held in scalar registers: read again at a load, the arguments would put
+  // a scalar wait, which is also one for LDS, into the unit loop)
+  typedef const __attribute__((address_space(1))) uint8_t* global_bytes;
+  global_bytes ids = (global_bytes)pt.idx;
+  int64_t rows = pt.N;
+  asm volatile("" : "+s"(ids), "+s"(rows));
   const uint32_t lane_off0 = (uint32_t)(nl * a.R);
   const uint32_t tile_stride = (uint32_t)(16 * a.R);
   uint32_t buf[L][DW];
@@ -175,9 +183,9 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   };
   auto load_unit = [&](int slot, int u, int t) {
     const int64_t tile = tile_of(u / T);
-    const bool live = u < nunits && tile * 16 + nl < pt.N && (!MASK || col_off[t] != ~0u);
+    const bool live = (u < nunits) & (tile * 16 + nl < rows) & (!MASK || col_off[t] != ~0u);
     const uint32_t off = (uint32_t)tile * tile_stride + lane_off0 + col_off[t];
-    load_chunk<BITS>(pt.idx + (live ? off : 0u), buf[slot]);
+    load_chunk<BITS>((const uint8_t*)(ids + (live ? off : 0u)), buf[slot]);
   };
 
   // ---- prologue.  The vector L1 returns loads in order, so an L2-resident
@@ -195,6 +203,17 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   const int mrow = nl < M ? nl : M - 1;  // x row this lane feeds to the A operand
   const uint8_t* xrow = xl + mrow * a.xs;
   half8_t xreg[kXInRegs ? T * SPC : 1];
+  // x on its way to the registers: a lane's slices are 16-byte pieces a chunk
+  // apart, so loading them straight would touch 64 segments per load.  Each
+  // wave copies its part of the rows to its own LDS region (global_load_lds,
+  // whole chunks per row) and reads its slices there: o_proj at 3 / 16 tokens
+  // 8.0 / 9.8 us with the loads straight, 6.0 / 6.5 us with the copies and the
+  // shorter window below.  Granule q of a row's
+  // NG lies in slot q ^ (row % NG), so that the rows of a read hit distinct
+  // banks.  The regions start at LDS address 0 and are done with before the
+  // codebook is stored.
+  constexpr int NG = 4 * T * SPC;          // 16-byte granules per row and wave
+  constexpr int XPL = NG / 4;              // copies per wave (64 granules each)
   Slice sl;
   const half_t* scb = pt.cb;
   int sC = pt.C;
@@ -228,13 +247,16 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
     if constexpr (kStageSlice) slice_fetch(scb, sC * D * 2 / 16, cst);
     else cb_fetch<D, MODE>(pt.cb, pt.C, cst);
     u32x4 xst[kXInRegs ? 1 : kXWordsPerThread];
+    uint8_t* xw = smem + wave * (XPL * 1024);
     if constexpr (kXInRegs) {
-      const half_t* xg = a.x + (int64_t)mrow * a.K;
 #pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const int c = RND ? c0 + ccol_raw(t) : ccol_raw(t) < CH ? ccol_raw(t) : CH - 1;
-#pragma unroll
-        for (int s = 0; s < SPC; ++s) xreg[t * SPC + s] = *reinterpret_cast<const half8_t*>(xg + c * (G * D) + s * 8);
+      for (int j = 0; j < XPL; ++j) {
+        const int i = j * kWave + lane;          // slot of the wave's region
+        const int row = i / NG, q = (i % NG) ^ (row % NG);
+        const int g4 = q / (T * SPC), ts = q % (T * SPC);  // K group, slice t * SPC + s of the lane
+        const int c = (RND ? c0 : 0) + (p * T + ts / SPC) * 4 + g4;
+        const half_t* src = a.x + (int64_t)(row < M ? row : M - 1) * a.K + (int64_t)c * (G * D) + ts % SPC * 8;
+        __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void*)(xw + j * 1024), 16, 0, 0);
       }
     } else {
 #pragma unroll
@@ -244,9 +266,25 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
         xst[k] = *x_word_src(w, wpr);
       }
     }
-    __syncthreads();
+    if constexpr (kXInRegs) {  // the bare barrier: a fence would wait for the copies
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      __syncthreads();
+    }
 #pragma unroll
-    for (int i = 0; i < L - 1; ++i) load_unit(i, i, i % T);
+    for (int i = 0; i < W; ++i) load_unit(i, i, i % T);
+    if constexpr (kXInRegs) {
+      __builtin_amdgcn_sched_barrier(0);
+      // the copies, not the index loads issued after them (vmcnt W, each one instruction)
+      __builtin_amdgcn_s_waitcnt((W & 15) | (0x7 << 4) | (0xF << 8));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < T * SPC; ++i)
+        xreg[i] = *reinterpret_cast<const half8_t*>(xw + (nl * NG + ((g * (T * SPC) + i) ^ (nl % NG))) * 16);
+      __syncthreads();  // every wave has read its x
+    }
 
     if constexpr (kStageSlice) slice_store(smem, scb, sC * D * 2 / 16, cst);
     else cb_store<D, MODE>(smem, pt.cb, pt.C, cst);
@@ -297,7 +335,7 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
       const int xw_total = wpr * M;
       __syncthreads();
 #pragma unroll
-      for (int i = 0; i < L - 1; ++i) load_unit(i, i, i % T);
+      for (int i = 0; i < W; ++i) load_unit(i, i, i % T);
       for (int base = threadIdx.x; base < xw_total; base += kXSlabBatch * blockDim.x) {
         u32x4 v[kXSlabBatch];
 #pragma unroll
@@ -317,56 +355,82 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
     float4_t acc0 = {0.f, 0.f, 0.f, 0.f};
     float4_t acc1 = {0.f, 0.f, 0.f, 0.f};
 
-    for (int base = 0; base < nunits; base += L) {
+    auto compute = [&](int slot, int u, int t) {
+      const uint32_t* w = buf[slot];
+      const int c = ccol_raw(t);
+      const bool cval = !MASK || c < chs;
+      const uint8_t* xa = xrow + (cval ? c : 0) * XCB;
+#pragma unroll
+      for (int s = 0; s < SPC; ++s) {
+        half8_t bop = gather8<BITS, D, MODE>(pt.cb, lane_off, w, s * (8 / D), sl);
+        half8_t aop;
+        if constexpr (kXInRegs) aop = xreg[t * SPC + s];
+        else aop = *reinterpret_cast<const half8_t*>(xa + s * 16);
+        if (!cval) {
+          bop = half8_t{};
+          aop = half8_t{};
+        }
+        if (s & 1) acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, bop, acc1, 0, 0, 0);
+        else acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, bop, acc0, 0, 0, 0);
+      }
+      if (t == T - 1) {
+        // lane l holds rows m = 4g .. 4g + 3 of column nl of the 16 x 16
+        // tile; the slabs of a row are summed in slab order by this lane
+        const int lrow = ((rounds ? (RND ? u / T % RT : 0) : u / T) * Q + q) * 16 + nl;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int m = 4 * g + k;
+          if (m < M) {
+            float* r = &red[(lrow * M + m) * PS + p];
+            *r = sb > sb0 ? *r + (acc0[k] + acc1[k]) : acc0[k] + acc1[k];
+          }
+        }
+        acc0 = float4_t{0.f, 0.f, 0.f, 0.f};
+        acc1 = float4_t{0.f, 0.f, 0.f, 0.f};
+      }
+      // a round of tiles done (the condition is the same in every wave: all
+      // waves have the same units): sum it while the next loads are in flight
+      if (rounds && t == T - 1 && (!RND || u / T % RT == RT - 1 || u / T == nrt - 1)) {
+        const int first = RND ? u / T / RT * RT : u / T;  // first tile of the round
+        __syncthreads();
+        sum_rows(first * Q * 16, 0, (u / T + 1 - first) * Q * 16);
+        __syncthreads();
+      }
+    };
+    // Unit k lives in slot k % L; W loads stay in flight.  Groups of L units
+    // whose loads all lie within the wave's units, then the last R < L + W
+    // units in code made for R (see the row-streaming kernel below: a test
+    // around each load would make the compiler wait for all of them).
+    int base = 0;
+    for (; base + L + W <= nunits; base += L) {
 #pragma unroll
       for (int i = 0; i < L; ++i) {
-        const int u = base + i;
-        const int t = i % T;
-        load_unit((i + L - 1) % L, u + L - 1, (i + L - 1) % T);
-        if (u < nunits) {
-          const uint32_t* w = buf[i];
-          const int c = ccol_raw(t);
-          const bool cval = !MASK || c < chs;
-          const uint8_t* xa = xrow + (cval ? c : 0) * XCB;
-#pragma unroll
-          for (int s = 0; s < SPC; ++s) {
-            half8_t bop = gather8<BITS, D, MODE>(pt.cb, lane_off, w, s * (8 / D), sl);
-            half8_t aop;
-            if constexpr (kXInRegs) aop = xreg[t * SPC + s];
-            else aop = *reinterpret_cast<const half8_t*>(xa + s * 16);
-            if (!cval) {
-              bop = half8_t{};
-              aop = half8_t{};
-            }
-            if (s & 1) acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, bop, acc1, 0, 0, 0);
-            else acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, bop, acc0, 0, 0, 0);
-          }
-          if (t == T - 1) {
-            // lane l holds rows m = 4g .. 4g + 3 of column nl of the 16 x 16
-            // tile; the slabs of a row are summed in slab order by this lane
-            const int lrow = ((rounds ? (RND ? u / T % RT : 0) : u / T) * Q + q) * 16 + nl;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              const int m = 4 * g + k;
-              if (m < M) {
-                float* r = &red[(lrow * M + m) * PS + p];
-                *r = sb > sb0 ? *r + (acc0[k] + acc1[k]) : acc0[k] + acc1[k];
-              }
-            }
-            acc0 = float4_t{0.f, 0.f, 0.f, 0.f};
-            acc1 = float4_t{0.f, 0.f, 0.f, 0.f};
-          }
-        }
-        // a round of tiles done (the condition is the same in every wave:
-        // all waves have the same units): sum it while the next round's
-        // loads are in flight
-        if (rounds && t == T - 1 && u < nunits && (!RND || u / T % RT == RT - 1 || u / T == nrt - 1)) {
-          const int first = RND ? u / T / RT * RT : u / T;  // first tile of the round
-          __syncthreads();
-          sum_rows(first * Q * 16, 0, (u / T + 1 - first) * Q * 16);
-          __syncthreads();
-        }
+        load_unit((i + W) % L, base + i + W, (i + W) % T);
+        compute(i, base + i, i % T);
       }
+    }
+    auto last = [&](auto rc) __attribute__((always_inline)) {
+      constexpr int R = decltype(rc)::value;
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        if (i + W < R) load_unit((i + W) % L, base + i + W, (i + W) % T);
+        compute(i % L, base + i, i % T);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // nunits is a multiple of T, and so is the rest
+    static_assert(L + W - 1 <= 9, "one case per possible remainder");
+    switch (nunits - base) {
+      case 1: if constexpr (1 % T == 0) last(std::integral_constant<int, 1>{}); break;
+      case 2: if constexpr (2 % T == 0) last(std::integral_constant<int, 2>{}); break;
+      case 3: if constexpr (3 % T == 0) last(std::integral_constant<int, 3>{}); break;
+      case 4: if constexpr (4 % T == 0) last(std::integral_constant<int, 4>{}); break;
+      case 5: if constexpr (5 % T == 0) last(std::integral_constant<int, 5>{}); break;
+      case 6: if constexpr (6 % T == 0 && L + W > 6) last(std::integral_constant<int, 6>{}); break;
+      case 7: if constexpr (7 % T == 0 && L + W > 7) last(std::integral_constant<int, 7>{}); break;
+      case 8: if constexpr (8 % T == 0 && L + W > 8) last(std::integral_constant<int, 8>{}); break;
+      case 9: if constexpr (9 % T == 0 && L + W > 9) last(std::integral_constant<int, 9>{}); break;
+      default: break;
     }
   }
   if (rounds) return;

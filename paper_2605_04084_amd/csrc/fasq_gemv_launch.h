@@ -394,7 +394,10 @@ hipError_t launch_gemv_bits(const Problem* ps, int count, const DeviceInfo& dev,
   }
   if (nwg > 0x7fffffff || tw * 16 > 0x7fffffff) return hipErrorNotSupported;
   if (round_tiles > tw) round_tiles = tw;
-  const int lds = (int)(cb_bytes + x_bytes + (rounds ? Q : round_tiles) * 16 * p.M * PS * 4);
+  // (x passes through LDS on its way to the registers: 16 rows of each wave's
+  // part, from address 0 and before anything else is there)
+  const int64_t x_pass = x_in_regs ? (int64_t)P * Q * (16 * 4 * T * (G * d / 8) * 16) : 0;
+  const int lds = (int)std::max(cb_bytes + x_bytes + (rounds ? Q : round_tiles) * 16 * p.M * PS * 4, x_pass);
 
   GemvArgs a = {};
   a.x = static_cast<const half_t*>(p.x);
