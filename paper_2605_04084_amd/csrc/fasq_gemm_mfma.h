@@ -244,9 +244,43 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64) void k_gemm_mfma(GemmArgs a) {
   __builtin_amdgcn_s_barrier();  // everyone's
   uint32_t idc[FN][HB / 4], idn[FN][HB / 4];
   read_ids(0, idc);
+  // Short sub-vectors (d <= 2: four or eight gathers per operand) on tiles whose
+  // waves hold one or two MFMA blocks read a whole chunk ahead instead: a
+  // k-step there is 32 or 64 cycles of MFMA behind an LDS round trip, so four
+  // steps in turn cost four of them.  The reads of chunk c + 1 follow the
+  // MFMAs of chunk c, and its ids are read before them.  d = 2, C = 256, us,
+  // step by step / a chunk ahead: 4096 x 4096 at 128 tokens 18.2 / 17.8, 512
+  // tokens 44.3 / 41.4, 4096 x 14336 at 128 tokens 44.0 / 41.0.  At d = 4
+  // (64 x 128 tile) the chunk is 2 to 9 % slower (512 tokens 27.9 / 29.2).
+  constexpr bool kChunkAhead = WAVES == 4 && FM * FN <= 2 && D <= 2;
+  if constexpr (kChunkAhead) {
+    Ops o[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) read_ops(o[t], 0, idc, t);
+    for (int c = 0; c < niter; ++c) {
+      wait_vmcnt<LPC * (NS - 3)>();  // this wave's copies of chunk c + 1
+      __builtin_amdgcn_s_barrier();  // everyone's; nobody reads chunk c - 1 any more
+      issue(chunk_of(c + NS - 1 < niter ? c + NS - 1 : niter - 1), (c + NS - 1) % NS);
+      const int nstage = (c + 1) % NS;
+      read_ids(nstage, idn);
+      __builtin_amdgcn_sched_barrier(0);
+      if (KG == 1 || c * KG + kg < nchunks) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+            for (int fn = 0; fn < FN; ++fn)
+              acc[fm][fn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(o[t].a[fm], o[t].b[fn], acc[fm][fn], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) read_ops(o[t], nstage, idn, t);
+    }
+  }
   Ops oa, ob;
-  read_ops(oa, 0, idc, 0);
-  for (int c = 0; c < niter; ++c) {
+  if constexpr (!kChunkAhead) read_ops(oa, 0, idc, 0);
+  for (int c = kChunkAhead ? niter : 0; c < niter; ++c) {
     const int stage = c % NS;
     const int nstage = (c + 1) % NS;
     const bool valid = c * KG + kg < nchunks;
