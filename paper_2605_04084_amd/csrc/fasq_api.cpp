@@ -136,7 +136,7 @@ fasq_status run(const Problem& p, Regime regime, hipStream_t stream, void* works
   e = hipErrorNotSupported;
   if (!force_generic()) {
     // a decode call with a workspace goes to the GEMM where that is faster
-    const bool to_gemm = regime == Regime::kGemv && workspace != nullptr && decode_prefers_gemm(p, dev) &&
+    const bool to_gemm = regime == Regime::kGemv && workspace != nullptr && decode_prefers_gemm(p, dev, workspace_bytes) &&
                          workspace_bytes >= gemm_workspace_bytes(p, dev);
     if (regime == Regime::kGemv && !to_gemm) {
       // the workspace also lets the 16-row-tile decode kernel split K

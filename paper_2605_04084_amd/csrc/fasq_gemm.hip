@@ -237,13 +237,15 @@ bool gemm_plan(const Problem& p, const DeviceInfo& dev, GemmPlan* out) {
 // LDS or registers (gate_proj 16 tokens: 15.9 against 25.3 us), or a
 // codebook the GEMM has to gather from global memory (65536 entries), the
 // decode kernel is the faster one.
-bool decode_prefers_gemm(const Problem& p, const DeviceInfo& dev) {
+bool decode_prefers_gemm(const Problem& p, const DeviceInfo& dev, int64_t workspace_bytes) {
   if (p.M < kGemmFromTokens || p.M > kGemvMaxTokens || !gemv_x_slabbed(p)) return false;
   // K segments with x in registers, enough of them to fill the CUs: the decode
   // kernel (down_proj 4096 x 14336 at 12 / 16 tokens 15.4 / 17.1 against 26.2 /
   // 25.8 us on the GEMM)
   const GemvSplit sp = gemv_split_plan(p);
-  if (sp.regs && (p.N + 15) / 16 * sp.nseg >= dev.num_cus) return false;
+  if (sp.regs && (p.N + 15) / 16 * sp.nseg >= dev.num_cus &&
+      (workspace_bytes < 0 || workspace_bytes >= (int64_t)sp.nseg * p.M * p.N * 4))
+    return false;
   GemmPlan pl;
   if (!gemm_plan(p, dev, &pl)) return false;
   return pl.ksplit > 1 && (pl.mode == CB_REPL || pl.mode == CB_HALF || pl.mode == CB_LDS);

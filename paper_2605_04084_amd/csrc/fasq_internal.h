@@ -72,7 +72,8 @@ bool gemv_x_slabbed(const Problem& p);
 // Whether a decode call that has a workspace is faster on the prefill GEMM
 // with its K split (the measured crossover); see fasq_gemm.hip.
 constexpr int kGemmFromTokens = 12;
-bool decode_prefers_gemm(const Problem& p, const DeviceInfo& dev);
+// workspace_bytes < 0: whatever either needs.
+bool decode_prefers_gemm(const Problem& p, const DeviceInfo& dev, int64_t workspace_bytes = -1);
 // Workspace bytes with which the 16-row-tile decode kernel splits K over
 // workgroups for p (one matrix; 0 when it would not split).
 int64_t gemv_split_workspace_bytes(const Problem& p);
