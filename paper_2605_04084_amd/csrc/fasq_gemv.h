@@ -76,7 +76,7 @@ struct GemvArgs {
   GemvPart part[kGemvMaxParts];
 };
 
-constexpr int kGemvPipe = 8;      // load units per wave in the software pipeline
+constexpr int kGemvPipe = 8;      // load slots per wave of the row-streaming kernels
 // Floats between the partial sums of consecutive (row, token) pairs in the
 // 16-row-tile kernel's LDS buffer, which holds P per pair (one per wave of a
 // row).  An odd stride for P > 1: with a stride of P = 16 floats the 64
@@ -107,9 +107,7 @@ constexpr int kXSlabBatch = 4;       // x words (16 B) in flight per thread when
 // sums are carried across the slabs in LDS (added in slab order by the same
 // lane, so the result stays deterministic).
 // MASK: some lanes see chunk columns past the end of their slab or row; their
-// operands are zeroed.  SLAB: x is staged in slabs (always with MASK); the
-// slab loop keeps more state live, so these variants run a shallower
-// pipeline (kGemvSlabPipe loads) to stay within the registers of 16 waves.
+// operands are zeroed.  SLAB: x is staged in slabs (always with MASK).
 // RND (not with SLAB): rounds of tiles (GemvArgs::round_sum), and K split over
 // gridDim.z segments of CHS chunk columns with x in registers.
 template <int BITS, int D, int T, int MODE, int MR, bool MASK, bool SLAB, bool RND>
