@@ -34,6 +34,8 @@ constexpr int kEncDirectThreads = 256;
 constexpr int kEncDirectPoints = 4;
 constexpr int kEncDirectMax = 64;                    // codewords up to which every distance is evaluated
 constexpr int kEncFineMax = 512;                     // codewords up to which the MFMA kernel keeps blocks of 8
+constexpr int kEncWholeGroups = 3;                   // groups of points after one with many open points that skip the minima
+constexpr int kEncBlock = 8;                         // codewords per block where every distance is evaluated
 constexpr int kEncSumThreads = 1024;
 constexpr int kEncSumBytes = 150 * 1024;             // LDS for the cluster sums of a workgroup
 constexpr int kEncSumMaxRanges = 8;                  // passes over the points the tables are worth
@@ -94,6 +96,23 @@ __device__ __forceinline__ float sq_dist(const float* p, const float* c) {
   return acc;
 }
 
+// The same with the codeword in fp16.  From four components on p_i - c_i is an
+// fma by minus one (the same bits), which takes a half operand as it is
+// (v_fma_mix): 2048 x 2048, d = 4, C = 4096, every distance 2.86 -> 2.75 ms;
+// d = 2, C = 256 0.24 -> 0.27 ms.
+template <int D>
+__device__ __forceinline__ float sq_dist_half(const float* p, const half_t* c, float minus_one) {
+#pragma clang fp contract(off)
+  float acc = 0.f;
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    const float ci = static_cast<float>(c[i]);
+    const float diff = D >= 4 ? __builtin_fmaf(ci, minus_one, p[i]) : p[i] - ci;
+    acc = i == 0 ? diff * diff : acc + diff * diff;
+  }
+  return acc;
+}
+
 // Codewords in LDS: DP halves each (d padded with zeros), 64 to a superblock,
 // and one unused read's worth after each superblock, so that lanes that read
 // the same place of different superblocks spread over the banks.
@@ -128,6 +147,17 @@ __device__ __forceinline__ void global_vector(const half_t* __restrict__ src, in
   } else {
 #pragma unroll
     for (int i = 0; i < DP; ++i) c[i] = i < d ? static_cast<float>(src[k * d + i]) : 0.f;
+  }
+}
+
+// Vector k of d halves, padded with zeros.
+template <int DP>
+__device__ __forceinline__ void half_vector(const half_t* __restrict__ src, int64_t k, int d, half_t* v) {
+  if (d == DP) {  // one wide load, at any alignment
+    __builtin_memcpy(v, src + k * DP, DP * 2);
+  } else {
+#pragma unroll
+    for (int i = 0; i < DP; ++i) v[i] = i < d ? src[k * d + i] : static_cast<half_t>(0.f);
   }
 }
 
@@ -196,6 +226,186 @@ __global__ __launch_bounds__(kEncDirectThreads) void k_enc_direct(const half_t* 
   }
 }
 
+// FN tiles of enc_every_distance, with the codebook in LDS at address 0 (LDS)
+// or in global memory.  DE: components that count.
+template <int DP, int FN, bool LDS, int DE>
+__device__ __forceinline__ void enc_every_pass(const half_t* __restrict__ w, int64_t P, int d,
+                                               const half_t* __restrict__ cb, int C, uint32_t* __restrict__ assign,
+                                               int64_t p0) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int lane = threadIdx.x % kWave, h = lane >> 5, col = lane & 31;
+  const float inf = __builtin_inff();
+  float bottom = -inf, minus_one = -1.f;
+  asm volatile("" : "+v"(bottom), "+v"(minus_one));
+  auto codeword = [&](int k, half_t* c) {
+    if constexpr (LDS) __builtin_memcpy(c, smem + EncTile<DP>::at(k), DP * 2);
+    else half_vector<DP>(cb, k, d, c);
+  };
+  float pv[FN][DP], best[FN];
+  int blk[FN];
+#pragma unroll
+  for (int f = 0; f < FN; ++f) {
+    const int64_t p = p0 + f * 32 + col;
+    global_vector<DP>(w, p < P ? p : P - 1, d, pv[f]);
+    best[f] = inf;
+    blk[f] = 0;
+  }
+  auto block = [&](int k, bool tail) {
+    float v[FN];
+#pragma unroll
+    for (int j = 0; j < kEncBlock; j += 2) {
+      half_t c0[DP], c1[DP];
+      codeword(!tail || k + j < C ? k + j : C - 1, c0);
+      codeword(!tail || k + j + 1 < C ? k + j + 1 : C - 1, c1);
+#pragma unroll
+      for (int f = 0; f < FN; ++f) {
+        const float s0 = sq_dist_half<DE>(pv[f], c0, minus_one), s1 = sq_dist_half<DE>(pv[f], c1, minus_one);
+        v[f] = j == 0 ? __builtin_fminf(s0, s1) : __builtin_fminf(__builtin_fminf(v[f], s0), s1);
+      }
+    }
+#pragma unroll
+    for (int f = 0; f < FN; ++f) {  // strict: the lowest block keeps a tie
+      blk[f] = v[f] < best[f] ? k : blk[f];
+      best[f] = __builtin_amdgcn_fmed3f(v[f], best[f], bottom);
+    }
+  };
+  int k = kEncBlock * h;
+  for (; k + kEncBlock <= C; k += 2 * kEncBlock) block(k, false);
+  if (k < C) block(k, true);
+#pragma unroll
+  for (int f = 0; f < FN; ++f) {
+    uint32_t bk = 0;
+    for (int j = kEncBlock - 1; j >= 0; --j) {
+      const int kk = blk[f] + j < C ? blk[f] + j : C - 1;
+      half_t c[DP];
+      codeword(kk, c);
+      if (best[f] < inf && sq_dist_half<DE>(pv[f], c, minus_one) == best[f]) bk = (uint32_t)kk;
+    }
+    const float ob = __shfl_xor(best[f], 32, kWave);
+    const uint32_t ok = (uint32_t)__shfl_xor((int)bk, 32, kWave);
+    if (ob < best[f] || (ob == best[f] && ok < bk)) bk = ok;
+    const int64_t p = p0 + f * 32 + col;
+    if (p < P && h == 0) assign[p] = bk;
+  }
+}
+
+// Every distance of the wave's FN tiles of 32 points from p0 on, where the
+// minima of k_enc_assign leave many of them open (repeated codewords, weights
+// with a large common offset, many codewords for d = 1).  A lane takes its
+// point of each tile and the blocks of kEncBlock codewords of its half: one
+// codeword read serves FN points, a block's minimum takes one v_min3 for two
+// distances, and the codeword is looked for in the smallest block at the end.
+// Bound by vector issue (12 to 13 instructions a pair at d = 4, 7 at d = 2).
+// One assignment and update of such points, with each point's codebook walked
+// by its own two lanes / this: 2048 x 2048, d = 2, C = 256, offset 0.5 758 / 251
+// us, half of the sub-vectors pruned 756 / 257; 1024 x 1024, d = 1, C = 1024
+// 605 / 252, half pruned 800 / 226; d = 4, C = 65536, 512 x 2048, offset 31.4 /
+// 16.8 ms; 2048 x 2048, d = 4, C = 4096, offset 3.74 / 2.74 ms.  (A function of
+// its own: its registers are not the matrix-core loop's.)
+template <int DP, int FN, bool ONE>
+__device__ __attribute__((noinline)) void enc_every_distance(const half_t* __restrict__ w, int64_t P, int d,
+                                                             const half_t* __restrict__ cb, int C,
+                                                             uint32_t* __restrict__ assign, int64_t p0, bool bad) {
+  constexpr int NF = DP >= 8 && FN > 2 ? 2 : FN;  // tiles at a time (registers)
+  for (int f = 0; f < FN; f += NF) {
+    const int64_t pf = p0 + f * 32;
+    if (ONE && !bad) {
+      if (DP == 2 && d == 1) enc_every_pass<DP, NF, ONE, 1>(w, P, d, cb, C, assign, pf);
+      else enc_every_pass<DP, NF, ONE, DP>(w, P, d, cb, C, assign, pf);
+    } else {
+      if (DP == 2 && d == 1) enc_every_pass<DP, NF, false, 1>(w, P, d, cb, C, assign, pf);
+      else enc_every_pass<DP, NF, false, DP>(w, P, d, cb, C, assign, pf);
+    }
+  }
+}
+
+// NP of a wave's open points (bits of lo and hi, which lose them; where fewer
+// are left the last one is repeated), the codewords dealt to the lanes.
+template <int DP, bool ONE, int NP>
+__device__ __forceinline__ void enc_open_batch(const half_t* __restrict__ w, int d, const half_t* __restrict__ cb,
+                                               int C, uint32_t* __restrict__ assign, int64_t p0, bool bad,
+                                               uint64_t& lo, uint64_t& hi) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int lane = threadIdx.x % kWave;
+  int q[NP];
+  float pv[NP][DP], best[NP];
+  uint32_t bk[NP];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    if (lo) {
+      q[j] = __ffsll((unsigned long long)lo) - 1;
+      lo &= lo - 1;
+    } else if (hi) {
+      q[j] = __ffsll((unsigned long long)hi) + 63;
+      hi &= hi - 1;
+    } else {
+      q[j] = q[j > 0 ? j - 1 : 0];
+    }
+    global_vector<DP>(w, p0 + q[j], d, pv[j]);
+#pragma unroll
+    for (int i = 0; i < DP; ++i)  // alike in all lanes: scalar registers
+      pv[j][i] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, pv[j][i])));
+    best[j] = __builtin_inff();
+    bk[j] = 0;
+  }
+  auto scan = [&](auto lds) {
+    for (int k = lane; k < C; k += kWave) {
+      float c[DP];
+      if constexpr (decltype(lds)::value) lds_codeword<DP>(smem, k, c);
+      else global_vector<DP>(cb, k, d, c);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        const float dist = sq_dist<DP>(pv[j], c);
+        bk[j] = dist < best[j] ? (uint32_t)k : bk[j];  // strict: the lowest index keeps a tie
+        best[j] = dist < best[j] ? dist : best[j];
+      }
+    }
+  };
+  if (ONE && !bad) scan(std::integral_constant<bool, ONE>{});
+  else scan(std::false_type{});
+  auto merge = [&](float& b, uint32_t& k, float give_b, uint32_t give_k, int m) {
+    const float ob = __shfl_xor(give_b, m, kWave);
+    const uint32_t ok = (uint32_t)__shfl_xor((int)give_k, m, kWave);
+    const bool take = ob < b || (ob == b && ok < k);
+    b = take ? ob : b;
+    k = take ? ok : k;
+  };
+  // each step halves the points a lane keeps, then the lanes of its one
+#pragma unroll
+  for (int m = kWave / 2, n = NP / 2; m > 0; m /= 2, n /= 2) {
+    if (n == 0) {
+      merge(best[0], bk[0], best[0], bk[0], m);
+    } else {
+      const bool up = lane & m;
+#pragma unroll
+      for (int j = 0; j < n; ++j) {
+        const float gb = up ? best[j] : best[j + n];
+        const uint32_t gk = up ? bk[j] : bk[j + n];
+        best[j] = up ? best[j + n] : best[j];
+        bk[j] = up ? bk[j + n] : bk[j];
+        merge(best[j], bk[j], gb, gk, m);
+      }
+    }
+  }
+  int mine = q[0];  // (a repeated point is written alike)
+#pragma unroll
+  for (int j = 1; j < NP; ++j) mine = lane / (kWave / NP) == j ? q[j] : mine;
+  if (lane % (kWave / NP) == 0) assign[p0 + mine] = bk[0];
+}
+
+// The few open points of a wave's tiles (one bit each): four share a codeword
+// read, the last one or two take it alone.
+template <int DP, bool ONE>
+__device__ __attribute__((noinline)) void enc_open_points(const half_t* __restrict__ w, int d,
+                                                          const half_t* __restrict__ cb, int C,
+                                                          uint32_t* __restrict__ assign, int64_t p0, bool bad,
+                                                          uint64_t lo, uint64_t hi) {
+  while (lo | hi) {
+    if (__popcll(lo) + __popcll(hi) > 2) enc_open_batch<DP, ONE, 4>(w, d, cb, C, assign, p0, bad, lo, hi);
+    else enc_open_batch<DP, ONE, 1>(w, d, cb, C, assign, p0, bad, lo, hi);
+  }
+}
+
 // Assignment of every point to its nearest codeword on the matrix cores.
 //
 // The defined distance costs 3 d + 2 vector operations per (point, codeword)
@@ -210,9 +420,11 @@ __global__ __launch_bounds__(kEncDirectThreads) void k_enc_direct(const half_t* 
 //   * Every codeword that can win has s <= min s + tau.  A lane whose b1 lies
 //     in that range evaluates the defined distance of that block's codewords;
 //     the two lanes of a point are merged by (distance, id).
-//   * If b2 lies in the range too (or the minimum is not finite), the point's
-//     whole codebook is evaluated: by the wave together for a few points, by
-//     each point's two lanes for many.
+//   * If b2 lies in the range too (or the minimum is not finite), the point is
+//     open: its whole codebook is evaluated, four points at a time with the
+//     codewords dealt to the lanes.  Where a tile has more of them than that
+//     is worth (open_max), every distance of the wave's points is, and of its
+//     next kEncWholeGroups groups without the minima.
 // tau: fp32 sums of d + 1 terms differ from the exact s by at most
 // (d + 2) 2^-22 (|p| + |c|)^2 / 2 whatever the order and rounding of the
 // additions (one ulp each), and the defined distance from the exact one by
@@ -245,19 +457,21 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
   const int ntiles = ONE ? 1 : (C + tile_cap - 1) / tile_cap;
   uint8_t* cw = smem;
   float* norms = reinterpret_cast<float*>(smem + (tile_cap / kEncSuper * Tile::SB + 15) / 16 * 16);
-  int* odd = reinterpret_cast<int*>(norms + tile_cap);  // ONE: the tile holds padding or non-finite codewords
+  int* odd = reinterpret_cast<int*>(norms + tile_cap);  // ONE: the tile holds non-finite codewords
 
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int h = lane >> 5, col = lane & 31;
   const float inf = __builtin_inff();
 
-  auto stage = [&](int k0, int nk) {  // codewords [k0, k0 + nk), padded to whole superblocks
+  // codewords [k0, k0 + nk), padded to whole superblocks by the last one (with
+  // an infinite norm; where its distance ties, the lower index has it)
+  auto stage = [&](int k0, int nk) {
     const int n = (nk + kEncSuper - 1) / kEncSuper * kEncSuper;
     for (int k = threadIdx.x; k < n; k += blockDim.x) {
       float c[DP];
       float norm = 0.f;
-      bool ok = k < nk;
-      global_vector<DP>(cb, k0 + (k < nk ? k : 0), d, c);
+      bool ok = true;
+      global_vector<DP>(cb, k0 + (k < nk ? k : nk - 1), d, c);
 #pragma unroll
       for (int i = 0; i < DP; ++i) {
         norm = __builtin_fmaf(c[i], c[i], norm);
@@ -271,7 +485,7 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
         v[1] = ok ? static_cast<half_t>(c[i + 1]) : static_cast<half_t>(0.f);
         *reinterpret_cast<uint32_t*>(q + i * 2) = as_u32(v);
       }
-      norms[k] = ok ? 0.5f * norm : inf;
+      norms[k] = ok && k < nk ? 0.5f * norm : inf;
       if (ONE && !ok) *odd = 1;
     }
   };
@@ -308,12 +522,17 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
     stage(0, C);
     __syncthreads();
   }
-  const bool check = ONE && *odd != 0;
+  const bool bad = ONE && *odd != 0;
   // opaque infinities: minima that start from one take three operands from
   // the first step on (v_min3 throughout), and the median with the other is
   // the minimum of two values without the instruction that quiets a NaN
   float top = inf, bottom = -inf;
   asm volatile("" : "+v"(top), "+v"(bottom));
+
+  // Vector instructions: an open point costs C / 64 rounds of 3 d + 5 and about
+  // 150 for its merge, every distance of a tile C / 2 times 3 d + 1.
+  const int open_max = (int)((int64_t)(C / 2) * (3 * d + 1) / ((C / 64) * (3 * d + 5) + 150));
+  int skip = 0;  // groups to come whose every distance is evaluated straight away
 
   const int64_t group = (int64_t)kEncWaves * FN * 32;
   for (int64_t g0 = blockIdx.x * group; g0 < P; g0 += (int64_t)gridDim.x * group) {
@@ -338,6 +557,8 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
       b1[f] = b2[f] = inf;
       i1[f] = 0;
     }
+    const bool skipped = skip > 0;
+    skip -= skipped;
     for (int t = 0; t < ntiles; ++t) {
       const int k0 = t * tile_cap;
       const int nk = C - k0 < tile_cap ? C - k0 : tile_cap;
@@ -346,6 +567,7 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
         stage(k0, nk);
         __syncthreads();
       }
+      if (skipped) continue;
       for (int k = 0; k < nk; k += 32) {
         const half8_t a = read_rows(k);
         const float16_t n = read_norms(k);
@@ -365,19 +587,42 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
         }
       }
     }
+    // the wave's points, and those that the minima leave open, per tile
+    half_t ph[FN][DP];
+    float thr[FN];
+    uint32_t open[FN];
+#pragma unroll
+    for (int f = 0; f < FN; ++f) {
+      const int64_t p = p0 + f * 32 + col;
+      half_vector<DP>(w, p < P ? p : P - 1, d, ph[f]);
+    }
+    bool whole = skipped, some = false;
+#pragma unroll
+    for (int f = 0; f < FN; ++f) {
+      float pn = 0.f;
+#pragma unroll
+      for (int i = 0; i < DP; ++i) pn = __builtin_fmaf(static_cast<float>(ph[f][i]), static_cast<float>(ph[f][i]), pn);
+      const float gb = __builtin_fminf(b1[f], __shfl_xor(b1[f], 32, kWave));
+      const float r = 2.01f * __builtin_amdgcn_sqrtf(pn) + 1.01f * __builtin_amdgcn_sqrtf(__builtin_fmaxf(pn + 2.f * gb, 0.f));
+      thr[f] = gb + r * r * ((float)(d + 3) * 4.76837158203125e-7f);  // 2^-21
+      // not (x < y): true for NaN as well
+      const bool slow = !(__builtin_fabsf(gb) < inf) || !(b2[f] > thr[f]);
+      const uint64_t both = __ballot(slow && p0 + f * 32 + col < P);
+      open[f] = (uint32_t)(both | (both >> 32));
+      some = some || open[f] != 0;
+      whole = whole || __popc(open[f]) > open_max;
+    }
+    if (whole) {
+      if (!skipped) skip = kEncWholeGroups;
+      enc_every_distance<DP, FN, ONE>(w, P, d, cb, C, assign, p0, bad);
+      continue;
+    }
 #pragma unroll
     for (int f = 0; f < FN; ++f) {
       const int64_t p = p0 + f * 32 + col;
       float pv[DP];
-      global_vector<DP>(w, p < P ? p : P - 1, d, pv);
-      float pn = 0.f;
 #pragma unroll
-      for (int i = 0; i < DP; ++i) pn = __builtin_fmaf(pv[i], pv[i], pn);
-      const float gb = __builtin_fminf(b1[f], __shfl_xor(b1[f], 32, kWave));
-      const float r = 2.01f * __builtin_sqrtf(pn) + 1.01f * __builtin_sqrtf(__builtin_fmaxf(pn + 2.f * gb, 0.f));
-      const float thr = gb + r * r * ((float)(d + 3) * 4.76837158203125e-7f);  // 2^-21
-      // not (x < y): true for NaN as well
-      const bool slow = !(__builtin_fabsf(gb) < inf) || !(b2[f] > thr);
+      for (int i = 0; i < DP; ++i) pv[i] = static_cast<float>(ph[f][i]);
       float best = inf;
       uint32_t bk = 0;
       auto consider = [&](int k) {  // strict: the lowest index keeps a tie
@@ -385,21 +630,15 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
         if constexpr (ONE) lds_codeword<DP>(cw, k, c);
         else global_vector<DP>(cb, k, d, c);
         const float dist = sq_dist<DP>(pv, c);
-        // (an infinite norm in LDS: padding, or a codeword staged as zeros)
-        if (dist < best && (!check || norms[k] < inf)) {
+        // (an infinite norm in LDS: a codeword staged as zeros, or padding)
+        if (dist < best && (!bad || norms[k] < inf)) {
           best = dist;
           bk = (uint32_t)k;
         }
       };
-      uint64_t todo = __ballot(slow);
-      todo = (todo | (todo >> 32)) & 0xFFFFFFFFull;  // points of the tile
-      const bool many = __popcll(todo) > 20;
-      if (many) {
-        for (int k = 0; k < C; k += 32)
-          for (int i = 0; i < 16; ++i) consider(ONE || k + row_of(i) < C ? k + row_of(i) : C - 1);
-      } else if (b1[f] <= thr) {
+      if (b1[f] <= thr[f]) {
         const int k = i1[f] / SUB * 32, i0 = i1[f] % SUB * BL;
-        if (!ONE || check) {
+        if (!ONE || bad) {
           for (int i = 0; i < BL; ++i) {
             const int kk = k + (i0 / 4) * 8 + row_of(i);  // i0 is a multiple of 4
             consider(ONE || kk < C ? kk : C - 1);
@@ -421,38 +660,16 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_enc_assign(const half_t* __r
           }
         }
       }
-      if (!many) {
-        while (todo) {  // one point at a time, the codewords dealt to the lanes
-          const int j = __ffsll((unsigned long long)todo) - 1;
-          todo &= todo - 1;
-          float keep[DP];
-          const float kbest = best;
-          const uint32_t kbk = bk;
-#pragma unroll
-          for (int i = 0; i < DP; ++i) {
-            keep[i] = pv[i];
-            pv[i] = __shfl(pv[i], j, kWave);
-          }
-          best = inf;
-          bk = 0;
-          for (int k = lane; k < C; k += kWave) consider(k);
-#pragma unroll
-          for (int m = 1; m < kWave; m *= 2) {
-            const float ob = __shfl_xor(best, m, kWave);
-            const uint32_t ok = (uint32_t)__shfl_xor((int)bk, m, kWave);
-            if (ob < best || (ob == best && ok < bk)) { best = ob; bk = ok; }
-          }
-          const bool mine = col == j;
-          best = mine ? best : kbest;
-          bk = mine ? bk : kbk;
-#pragma unroll
-          for (int i = 0; i < DP; ++i) pv[i] = keep[i];
-        }
-      }
       const float ob = __shfl_xor(best, 32, kWave);
       const uint32_t ok = (uint32_t)__shfl_xor((int)bk, 32, kWave);
       if (ob < best || (ob == best && ok < bk)) bk = ok;
-      if (p < P && h == 0) assign[p] = bk;
+      if (p < P && h == 0 && !(open[f] >> col & 1)) assign[p] = bk;
+    }
+    if (some) {
+      uint64_t lo = 0, hi = 0;  // the open points of tiles 0 and 1, and 2 and 3
+#pragma unroll
+      for (int f = 0; f < FN; ++f) (f < 2 ? lo : hi) |= (uint64_t)open[f] << (f % 2 * 32);
+      enc_open_points<DP, ONE>(w, d, cb, C, assign, p0, bad, lo, hi);
     }
   }
 }

@@ -45,10 +45,10 @@ def check_encode(w, d, C, bits, init, iters, label):
 CASES = [
     # N, K, d, C, bits, iters
     (256, 512, 2, 256, 8, 5),     # cluster sums gathered in LDS per workgroup
-    (128, 512, 4, 4096, 12, 3),   # sums straight to global atomics
-    (256, 512, 4, 20000, 16, 2),  # codebook in five LDS tiles
+    (128, 512, 4, 4096, 12, 3),   # one LDS table of cluster sums per workgroup
+    (256, 512, 4, 20000, 16, 2),  # codebook in four LDS tiles
     (64, 256, 8, 256, 8, 4),
-    (100, 300, 3, 50, 8, 3),      # d = 3: the general-d kernel
+    (100, 300, 3, 50, 8, 3),      # every distance, d = 3 padded to 4
     (33, 64, 1, 16, 8, 6),
     (50, 36, 4, 9, 12, 4),        # odd 12-bit rows (pad nibble)
     (40, 64, 2, 64, 8, 0),        # no update: ids against the starting codebook
@@ -192,3 +192,108 @@ def test_encoded_layer_runs_through_the_matmul():
     # quantization error of the layer output against the dense fp16 weights, for the record
     dense = x.astype(np.float64) @ w.astype(np.float64).T
     print(f"[encode] layer rel error vs dense weights: {orc.relative_l2(y, dense):.3f}", flush=True)
+
+
+def nearest(w, d, cb):
+    """The defined assignment on the GPU by plain torch: fp32 differences,
+    squares and sums rounded one by one, the lowest index on ties."""
+    points, c = w.view(-1, d).float(), cb.float()
+    order = torch.arange(len(c), device=w.device, dtype=torch.int32)
+    out = torch.empty(len(points), dtype=torch.int64, device=w.device)
+    block = max(1, (1 << 26) // len(c))
+    for b in range(0, len(points), block):
+        p = points[b:b + block]
+        dist = torch.zeros((len(p), len(c)), device=w.device)
+        for i in range(d):
+            diff = p[:, i:i + 1] - c[None, :, i]
+            dist += diff * diff
+        dist[~(dist < float("inf"))] = float("inf")  # a non-finite codeword is never chosen
+        near = dist == dist.amin(1, keepdim=True)
+        out[b:b + block] = torch.where(near, order, len(c)).amin(1).long()
+    return out
+
+
+def weights(values, N, K, d):
+    """Weights whose nearest codeword the matrix-core pass decides (normal) or
+    leaves open: a large common offset, half of the sub-vectors pruned (the
+    starting codewords repeat zero), values on a lattice."""
+    g = torch.Generator(device="cuda").manual_seed(N + K + d)
+    w = torch.randn((N, K), generator=g, device="cuda") * 0.02
+    if values == "offset":
+        w = w + 0.5
+    elif values == "pruned":
+        keep = torch.rand((N * K // d, 1), generator=g, device="cuda") < 0.5
+        w = (w.view(-1, d) * keep).view(N, K)
+    elif values == "lattice":
+        w = (w / 0.01).round() * 0.01
+    return w.half()
+
+
+def first_codewords(w, d, C):
+    points = w.view(-1, d)
+    return points[torch.linspace(0, len(points) - 1, C, device="cuda").long()].contiguous()
+
+
+# four point tiles per wave (from 524288 points on) and one, codebooks of one
+# LDS tile (blocks of 8 and of 16 codewords) and of several, padded d
+OPEN = [
+    # N, K, d, C, bits
+    (1031, 1024, 1, 300, 12),      # point count that fills no tile
+    (520, 1024, 1, 4096, 12),
+    (1040, 1024, 2, 256, 8),
+    (1037, 1030, 2, 1000, 12),
+    (1100, 1536, 3, 100, 8),
+    (2100, 1024, 4, 4096, 12),     # the 12-bit format's codebook
+    (2080, 1024, 4, 6000, 16),     # two LDS tiles
+    (4201, 1024, 8, 257, 12),
+    (4200, 2048, 16, 520, 12),
+    (100, 1000, 2, 300, 12),
+    (64, 1024, 4, 20000, 16),
+    (90, 704, 11, 300, 12),
+]
+
+
+@pytest.mark.parametrize("values", ["normal", "offset", "pruned", "lattice"])
+@pytest.mark.parametrize("case", OPEN)
+def test_points_left_open_by_the_matrix_cores(case, values):
+    N, K, d, C, bits = case
+    print(f"[case] encode open {case} {values}", flush=True)
+    K = K // d * d
+    w = weights(values, N, K, d)
+    init = first_codewords(w, d, C)
+    if values == "lattice":
+        init[C // 3] = float("inf")  # codewords staged as zeros
+        init[C // 2, 0] = float("nan")
+    ref = nearest(w, d, init)
+    _, idx = fasq.pq_encode(w, d, bits, init, 0)
+    ids = orc.unpack_indices(to_np(idx), K // d, bits, C).reshape(-1)
+    assert np.array_equal(ids, ref.cpu().numpy()), int((ids != ref.cpu().numpy()).sum())
+
+
+def encode_ms(w, d, bits, init, calls=20):
+    ws = torch.empty(fasq.encode_workspace_bytes(*w.shape, d, len(init)), dtype=torch.uint8, device="cuda")
+    best = float("inf")
+    for _ in range(4):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            fasq.pq_encode(w, d, bits, init, 0, workspace=ws)
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / calls)
+    return best
+
+
+@pytest.mark.parametrize("d,C,values", [(1, 256, "pruned"), (1, 1024, "offset"), (2, 256, "offset"), (2, 256, "pruned"),
+                                        (4, 512, "pruned"), (8, 256, "pruned")])
+def test_open_points_cost_no_more_than_every_distance(d, C, values):
+    """Where the matrix-core pass leaves most points open, the encoder must not
+    take longer than evaluating every distance, which it does for codebooks
+    of up to 64 codewords: C / 64 times such a call (and a quarter, for the
+    pass itself and the spread of a timing)."""
+    N, K = 2048, 2048
+    w = weights(values, N, K, d)
+    every = encode_ms(w, d, 8, first_codewords(w, d, 64)) * (C / 64)
+    took = encode_ms(w, d, 12 if C > 256 else 8, first_codewords(w, d, C))
+    print(f"[time] d={d} C={C} {values}: {took * 1e3:.0f} us, every distance {every * 1e3:.0f} us", flush=True)
+    assert took <= 1.25 * every
