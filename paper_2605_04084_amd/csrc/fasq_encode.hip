@@ -36,6 +36,7 @@ constexpr int kEncDirectMax = 64;                    // codewords up to which ev
 constexpr int kEncFineMax = 512;                     // codewords up to which the MFMA kernel keeps blocks of 8
 constexpr int kEncWholeGroups = 3;                   // groups of points after one with many open points that skip the minima
 constexpr int kEncBlock = 8;                         // codewords per block where every distance is evaluated
+constexpr int kEncUpdateThreads = 256;               // at least the largest d
 constexpr int kEncSumThreads = 1024;
 constexpr int kEncSumBytes = 150 * 1024;             // LDS for the cluster sums of a workgroup
 constexpr int kEncSumMaxRanges = 8;                  // passes over the points the tables are worth
@@ -735,20 +736,24 @@ __global__ __launch_bounds__(kEncSumThreads) void k_enc_sum(const half_t* __rest
 }
 
 // New codewords: each non-empty cluster's rounded mean; empty ones are kept.
-// The sums and counts are cleared for the next iteration.
-__global__ void k_enc_update(uint16_t* __restrict__ cb, int64_t* __restrict__ sums, int64_t* __restrict__ counts,
-                             int C, int d) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= C) return;
-  const int64_t cnt = counts[k];
+// The sums and counts are cleared for the next iteration.  A thread takes one
+// component (a thread per codeword read its components one after the other,
+// about 0.5 us each), a workgroup whole codewords, so that a count is cleared
+// when all of its readers have it.
+__global__ __launch_bounds__(kEncUpdateThreads) void k_enc_update(uint16_t* __restrict__ cb, int64_t* __restrict__ sums,
+                                                                  int64_t* __restrict__ counts, int C, int d) {
+  const int per = kEncUpdateThreads / d;  // codewords per workgroup
+  const int local = threadIdx.x / d;
+  const int k = blockIdx.x * per + local;
+  const bool live = local < per && k < C;
+  const int64_t t = live ? (int64_t)k * d + (threadIdx.x - local * d) : 0;
+  const int64_t cnt = live ? counts[k] : 0;
+  const int64_t sum = sums[t];
+  __syncthreads();
   if (cnt == 0) return;
-  counts[k] = 0;
-  for (int i = 0; i < d; ++i) {
-    const int64_t t = (int64_t)k * d + i;
-    const double mean = (static_cast<double>(sums[t]) * kQInv) / static_cast<double>(cnt);
-    sums[t] = 0;
-    cb[t] = f64_to_f16_rne(mean);
-  }
+  sums[t] = 0;
+  if (threadIdx.x == local * d) counts[k] = 0;
+  cb[t] = f64_to_f16_rne((static_cast<double>(sum) * kQInv) / static_cast<double>(cnt));
 }
 
 // ids [N x S] (uint32) -> packed rows of R bytes.  One thread per id pair
@@ -860,6 +865,7 @@ hipError_t launch_sum(const half_t* w, int64_t P, int d, int C, const uint32_t* 
 hipError_t launch_assign(const half_t* w, int64_t P, int d, const half_t* cb, int C, uint32_t* assign, int64_t* sums,
                          int64_t* counts, bool accum, const DeviceInfo& dev, hipStream_t stream) {
   if (C <= kEncDirectMax) {
+    if (d == 1) return launch_direct<1>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
     if (d <= 2) return launch_direct<2>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
     if (d <= 4) return launch_direct<4>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
     if (d <= 8) return launch_direct<8>(w, P, d, cb, C, assign, sums, counts, accum, dev, stream);
@@ -907,7 +913,8 @@ hipError_t launch_encode(const EncodeProblem& e, const DeviceInfo& dev, hipStrea
   for (int it = 0; it < e.iters; ++it) {
     err = launch_assign(w, P, d, reinterpret_cast<const half_t*>(cb), C, assign, sums, counts, true, dev, stream);
     if (err != hipSuccess) return err;
-    err = launch_kernel(k_enc_update, dim3(grid_for(C, 64)), dim3(64), 0, stream, cb, sums, counts, C, d);
+    err = launch_kernel(k_enc_update, dim3((unsigned)((C + kEncUpdateThreads / d - 1) / (kEncUpdateThreads / d))),
+                        dim3(kEncUpdateThreads), 0, stream, cb, sums, counts, C, d);
     if (err != hipSuccess) return err;
   }
   err = launch_assign(w, P, d, reinterpret_cast<const half_t*>(cb), C, assign, sums, counts, false, dev, stream);
