@@ -194,6 +194,7 @@ __global__ __launch_bounds__(kEncDirectThreads) void k_enc_direct(const half_t* 
       best[j] = __builtin_inff();
       bk[j] = 0;
     }
+#pragma unroll 4
     for (int k = 0; k < C; ++k) {
 #pragma unroll
       for (int j = 0; j < PPT; ++j) {

@@ -282,6 +282,53 @@ __global__ __launch_bounds__(kGenericWaves * kWave) void k_pq_generic(GenericArg
   }
 }
 
+// The same for calls of few values, a wave per output feature: the lanes take
+// the S sub-vectors, up to kRowsTokens tokens at once, scalar products in fp32.
+// Bound by the latency of its few serial loads, where k_pq_generic issues an
+// unrolled span whatever part of it is there (2500 instructions at a run-time
+// d).  Replayed from a graph, this / k_pq_generic (K x N): 1 token, 110 x 478,
+// d = 5 3.2 / 5.8 us, 336 x 848, d = 6, 12-bit ids 3.7 / 7.1; 2 tokens, 8 x 7,
+// d = 4 3.1 / 4.0; 4 tokens, 203 x 23, d = 7 5.1 / 6.4; but 8 tokens, 6 x 36,
+// d = 6 6.3 / 5.3 and 4 tokens, 112 x 1529, d = 4 4.4 / 3.4.
+constexpr int kRowsTokens = 8;
+constexpr int kRowsThreads = 256;
+
+template <int BITS>
+__global__ __launch_bounds__(kRowsThreads) void k_pq_generic_rows(const half_t* __restrict__ x, int M, int64_t K,
+                                                                  int64_t N, const uint8_t* __restrict__ idx,
+                                                                  int64_t R, int d, const half_t* __restrict__ cb,
+                                                                  int64_t cbs, half_t* __restrict__ y) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t S = K / d;
+  const int64_t n = blockIdx.x * (int64_t)(kRowsThreads / kWave) + threadIdx.x / kWave;
+  if (n >= N) return;
+  const uint8_t* row = idx + n * R;
+  for (int m0 = 0; m0 < M; m0 += kRowsTokens) {
+    const int mb = M - m0 < kRowsTokens ? M - m0 : kRowsTokens;
+    float acc[kRowsTokens];
+#pragma unroll
+    for (int j = 0; j < kRowsTokens; ++j) acc[j] = 0.f;
+    for (int64_t s = lane; s < S; s += kWave) {
+      const uint32_t u = load_id_bytes<BITS>(row, s, R);
+      const half_t* c = cb + s * cbs + (int64_t)u * d;
+      for (int i = 0; i < d; ++i) {
+        const float cv = static_cast<float>(c[i]);
+        const half_t* xp = x + m0 * K + s * d + i;
+#pragma unroll
+        for (int j = 0; j < kRowsTokens; ++j)
+          if (j < mb) acc[j] = __builtin_fmaf(static_cast<float>(xp[j * K]), cv, acc[j]);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kRowsTokens; ++j) {
+      if (j < mb) {
+        const float v = wave_sum(acc[j]);
+        if (lane == 0) y[(m0 + j) * N + n] = static_cast<half_t>(v);
+      }
+    }
+  }
+}
+
 static int grid_for(int64_t items, int per_block, int max_blocks) {
   int64_t b = (items + per_block - 1) / per_block;
   if (b > max_blocks) b = max_blocks;
@@ -340,9 +387,39 @@ hipError_t launch_generic_bits(const GenericArgs& a, int fm, hipStream_t stream)
   }
 }
 
+// Steps of k_pq_generic_rows (rounds of sub-vectors x d x 5/4 of the tokens and
+// three more for the id and the codeword), weighted by the features beyond a
+// round of its waves, up to which it is the faster one: 24 where k_pq_generic
+// has d as a constant (32 with 12-bit ids), 76 where it takes a run-time d or
+// 12-bit ids at d = 1 (whose runs start at half bytes).  Of 1350 random calls
+// around the line 30 were on the slower side, by 20 % at most.
+bool rows_faster(const Problem& p) {
+  if (p.M > 2 * kRowsTokens || p.N > 16384 || p.d > 16) return false;
+  const bool constant_d = p.d == 2 || p.d == 4 || p.d == 8 || (p.d == 1 && p.idx_bits != 12);
+  const int64_t most = !constant_d ? 76 : p.idx_bits == 12 ? 32 : 24;
+  const int64_t passes = (p.M + kRowsTokens - 1) / kRowsTokens;
+  const int64_t tokens = p.M < kRowsTokens ? p.M : kRowsTokens;
+  const int64_t steps = passes * ((p.S + kWave - 1) / kWave) * p.d * (tokens * 5 / 4 + 3);
+  return steps <= most && steps * p.N <= most * 2048;
+}
+
 }  // namespace
 
 hipError_t launch_generic(const Problem& p, const DeviceInfo& dev, hipStream_t stream) {
+  if (rows_faster(p)) {
+    if (plan_record("k_pq_generic_rows", {p.idx_bits})) return hipSuccess;
+    const dim3 grid((unsigned)((p.N + kRowsThreads / kWave - 1) / (kRowsThreads / kWave)));
+    const half_t* x = static_cast<const half_t*>(p.x);
+    const uint8_t* idx = static_cast<const uint8_t*>(p.idx);
+    const half_t* cb = static_cast<const half_t*>(p.codebook);
+    half_t* y = static_cast<half_t*>(p.y);
+    const int M = (int)p.M;
+    switch (p.idx_bits) {
+      case 8: return launch_kernel(k_pq_generic_rows<8>, grid, dim3(kRowsThreads), 0, stream, x, M, p.K, p.N, idx, p.R, p.d, cb, p.cb_stride, y);
+      case 12: return launch_kernel(k_pq_generic_rows<12>, grid, dim3(kRowsThreads), 0, stream, x, M, p.K, p.N, idx, p.R, p.d, cb, p.cb_stride, y);
+      default: return launch_kernel(k_pq_generic_rows<16>, grid, dim3(kRowsThreads), 0, stream, x, M, p.K, p.N, idx, p.R, p.d, cb, p.cb_stride, y);
+    }
+  }
   if (plan_record("k_pq_generic", {p.idx_bits})) return hipSuccess;
   // token tiles per workgroup: up to four share the gathers, fewer where the
   // grid would leave compute units idle

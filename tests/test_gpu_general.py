@@ -1,5 +1,5 @@
-"""GPU parity of the general kernel (the calls no tuned kernel takes) at the
-edges of its spans, runs and tiles, and at pointers of any alignment."""
+"""GPU parity of the general kernels (the calls no tuned kernel takes) at the
+edges of their spans, runs and tiles, and at pointers of any alignment."""
 
 import numpy as np
 import pytest
@@ -47,10 +47,42 @@ CASES = [
     (18, 312, 30, 24, 90, 12, False, (0, 0, 0)),    # one codeword per run
     (7, 200, 33, 40, 50, 8, False, (0, 1, 2)),      # codewords longer than a run
     (2, 350, 20, 35, 700, 16, True, (2, 0, 0)),
+    (17, 3, 1, 3, 2, 8, False, (0, 0, 0)),          # the smallest sizes with more tokens than the row kernel takes
+    (9, 99, 1000, 3, 256, 8, True, (0, 0, 0)),
+]
+
+# a wave per feature: few values per lane (one round of sub-vectors and more,
+# whole and not), a second block of tokens, odd 12-bit rows, any alignment
+ROWS = [
+    # M, K, N, d, C, bits, per subspace, byte offsets of x, ids and codebook
+    (1, 1, 1, 1, 1, 8, False, (0, 0, 0)),
+    (1, 64, 5, 1, 256, 8, False, (2, 1, 2)),
+    (2, 65, 7, 1, 300, 12, True, (2, 1, 2)),
+    (8, 130, 3, 1, 300, 12, False, (0, 0, 0)),
+    (16, 14, 2, 1, 512, 12, True, (0, 0, 2)),
+    (9, 5, 4, 1, 4096, 12, False, (0, 1, 0)),
+    (1, 110, 478, 5, 100, 8, False, (0, 0, 0)),
+    (1, 336, 848, 6, 4096, 12, False, (2, 1, 2)),
+    (3, 96, 2000, 3, 256, 8, True, (0, 0, 0)),
+    (7, 35, 30, 5, 5000, 16, False, (2, 0, 2)),
+    (1, 16, 3000, 2, 16, 8, True, (0, 3, 0)),
+    (3, 16, 9, 4, 90, 8, False, (2, 0, 0)),
+    (1, 144, 33, 9, 70, 12, True, (0, 1, 2)),
 ]
 
 
-@pytest.mark.parametrize("case", CASES)
+def test_small_calls_take_the_row_kernel(monkeypatch):
+    """The kernel of the few-value calls, and the sizes from which the matrix
+    cores are faster (its time grows with rounds x d x tokens)."""
+    monkeypatch.setenv("FASQ_FORCE_PATH", "generic")
+    rows = [fasq.plan("gemv", M, K, N, bits, d, C).startswith("k_pq_generic_rows<") for M, K, N, d, C, bits, *_ in ROWS]
+    assert all(rows), rows
+    for M, K, N, bits, d, C in [(4, 112, 1529, 8, 4, 256), (8, 6, 36, 16, 6, 5000), (1, 130, 9000, 8, 5, 256),
+                                (17, 3, 1, 8, 3, 2), (1, 4096, 100, 8, 2, 256), (1, 24, 20000, 12, 6, 1000)]:
+        assert not fasq.plan("gemv", M, K, N, bits, d, C).startswith("k_pq_generic_rows<"), (M, K, N, bits, d)
+
+
+@pytest.mark.parametrize("case", CASES + ROWS)
 def test_general_kernel_matches_oracle(case, monkeypatch):
     M, K, N, d, C, bits, per, (ox, oi, oc) = case
     print(f"[case] general {case}", flush=True)
