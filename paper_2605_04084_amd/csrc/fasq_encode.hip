@@ -237,8 +237,8 @@ __device__ __forceinline__ void enc_every_pass(const half_t* __restrict__ w, int
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int lane = threadIdx.x % kWave, h = lane >> 5, col = lane & 31;
   const float inf = __builtin_inff();
-  float bottom = -inf, minus_one = -1.f;
-  asm volatile("" : "+v"(bottom), "+v"(minus_one));
+  float minus_one = -1.f;
+  asm volatile("" : "+v"(minus_one));
   auto codeword = [&](int k, half_t* c) {
     if constexpr (LDS) __builtin_memcpy(c, smem + EncTile<DP>::at(k), DP * 2);
     else half_vector<DP>(cb, k, d, c);
@@ -266,9 +266,12 @@ __device__ __forceinline__ void enc_every_pass(const half_t* __restrict__ w, int
       }
     }
 #pragma unroll
-    for (int f = 0; f < FN; ++f) {  // strict: the lowest block keeps a tie
-      blk[f] = v[f] < best[f] ? k : blk[f];
-      best[f] = __builtin_amdgcn_fmed3f(v[f], best[f], bottom);
+    for (int f = 0; f < FN; ++f) {
+      // strict: the lowest block keeps a tie; selects, since the minimum of
+      // a block of NaN distances is a NaN and must leave the best as it is
+      const bool less = v[f] < best[f];
+      blk[f] = less ? k : blk[f];
+      best[f] = less ? v[f] : best[f];
     }
   };
   int k = kEncBlock * h;

@@ -270,6 +270,24 @@ def test_points_left_open_by_the_matrix_cores(case, values):
     assert np.array_equal(ids, ref.cpu().numpy()), int((ids != ref.cpu().numpy()).sum())
 
 
+@pytest.mark.parametrize("d,C,bits", [(1, 300, 12), (2, 256, 8), (4, 512, 12), (4, 6000, 16)])
+def test_whole_blocks_of_codewords_at_no_distance(d, C, bits):
+    """Runs of codewords whose distances are all NaN (a NaN component, or
+    infinities of weight and codeword) among points whose every distance is
+    evaluated: they are passed over like single ones."""
+    N, K = 300, 1024
+    w = weights("pruned", N, K, d)
+    init = first_codewords(w, d, C)
+    init[16:40] = float("nan")
+    init[64:96] = float("inf")
+    init[C - 20:] = float("nan")
+    w[7] = float("inf")  # at no finite distance from any codeword
+    ref = nearest(w, d, init)
+    _, idx = fasq.pq_encode(w, d, bits, init, 0)
+    ids = orc.unpack_indices(to_np(idx), K // d, bits, C).reshape(-1)
+    assert np.array_equal(ids, ref.cpu().numpy()), int((ids != ref.cpu().numpy()).sum())
+
+
 def encode_ms(w, d, bits, init, calls=20):
     ws = torch.empty(fasq.encode_workspace_bytes(*w.shape, d, len(init)), dtype=torch.uint8, device="cuda")
     best = float("inf")
