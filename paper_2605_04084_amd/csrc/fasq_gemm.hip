@@ -100,7 +100,9 @@ hipError_t launch_gemm_mode(const GemmArgs& a, int mode, int tile, int kg, int l
       if constexpr (gemm_big_tile_fits(BITS, D))
         return launch_gemm_variant<BITS, D, CB_HALF, 256, 256, 2, 4, kGemmTiles[0].ns, 1>(a, lds, stream);
       else return hipErrorNotSupported;
-    default: return launch_gemm_tile<BITS, D, CB_GLOBAL>(a, tile, kg, lds, stream);
+    default:  // single values from global memory: always k_gemm_gather
+      if constexpr (D == 1) return hipErrorNotSupported;
+      else return launch_gemm_tile<BITS, D, CB_GLOBAL>(a, tile, kg, lds, stream);
   }
 }
 
@@ -133,14 +135,33 @@ constexpr int kGemmMaxSplit = 8;
 constexpr int kGemmMinSplitChunks = 4;
 constexpr int kGatherMinSplitChunks = 8;
 // Codebooks gathered from global memory go to k_gemm_gather, which decodes
-// each tile of W_hat once per workgroup: 65536 entries, d = 4, 4096 x 4096 at
-// 64 / 128 / 512 / 2048 tokens 31 / 47 / 61 / 216 us against 59 / 69 / 244 /
-// 537 us on k_gemm_mfma (whose waves each gather their own operands).  It is
-// the faster one at every size measured; k_gemm_mfma keeps the calls whose
-// plan the tests fix: small matrices (fewer than kGatherMinIds ids: 70 x 1088
-// at 100 tokens 18 against 11 us) and more than one round of 128 x 256 tiles
-// (14336 x 4096 at 2048 tokens 1900 against 665 us).
-constexpr int64_t kGatherMinIds = 32768;
+// each tile of W_hat once per workgroup, where k_gemm_mfma's waves each gather
+// their own operands: 65536 entries, d = 4, 4096 x 4096 at 64 / 128 / 512 / 2048
+// tokens 31 / 47 / 61 / 216 us against 59 / 69 / 244 / 537 us, 14336 x 4096 at
+// 2048 tokens 665 against 1900 us, 70 x 1088 at 100 tokens 10 against 17 us.  Of
+// 8000 random calls (M to 4100, K to 4096, N to 14336, every id width and d) it
+// took 0.55 of k_gemm_mfma's time (geometric mean).  k_gemm_mfma is the faster
+// one for cheap codewords (d = 8, where one read brings a whole operand, and
+// d >= 2 from a book of L1 size: codebooks of no whole 16-byte words)
+//   * in its 256 x 256 tile (d = 4, 251 entries, 3148 x 2432 x 9324: 206 against 272 us),
+//   * for up to kGatherFewK values of K in the smaller tiles, which the longer pipeline
+//     does not pay for (d = 8, 64 x 9339 at 39 tokens: 4.7 against 6.1 us),
+//   * up to twice that where the gather tiles, half as wide, take another round of
+//     workgroups (d = 4, 251 entries, 256 x 10761 at 340 tokens: 12.2 against 17.1 us).
+// With this rule 34 of 7300 calls on k_gemm_gather were over 3 % slower there,
+// by 30 % at most.
+constexpr int64_t kGatherFewK = 128;
+constexpr int64_t kL1Bytes = 32 * 1024;
+
+bool gather_faster(const Problem& p, const DeviceInfo& dev, int tile, int64_t tiles, int gather, int64_t gather_tiles) {
+  const bool cheap = p.d == 8 || (p.d >= 2 && p.C * p.d * 2 <= kL1Bytes);
+  if (!cheap) return true;
+  if (tile == 0) return false;
+  auto rounds = [&](int64_t n) { return (n + dev.num_cus - 1) / dev.num_cus; };
+  const bool more_rounds = rounds(gather_tiles) > rounds(tiles);
+  if (p.K <= kGatherFewK) return !more_rounds && kGatherTiles[gather].bm == 256;
+  return !more_rounds || p.K > 2 * kGatherFewK;
+}
 
 bool gemm_plan(const Problem& p, const DeviceInfo& dev, GemmPlan* out) {
   const int d = p.d;
@@ -201,21 +222,28 @@ bool gemm_plan(const Problem& p, const DeviceInfo& dev, GemmPlan* out) {
   int64_t tiles = tiles_of(tile);
   int64_t min_chunks = (int64_t)kGemmMinSplitChunks * kg;
   out->gather = -1;
-  if (mode == CB_GLOBAL && p.N * p.S >= kGatherMinIds && (tile > 1 || tiles <= dev.num_cus)) {
-    // the tile with the fewest cycles over its rounds of workgroups: gathers
-    // at one lane per cycle, the X copy at 64 bytes
-    int64_t best = 0;
+  if (mode == CB_GLOBAL) {
+    // the tile with the fewest address cycles over its rounds of workgroups: a
+    // gather takes one a lane (two from L2 on end, see k_gemm_gather; the X
+    // copies wait in the same queue), the X copy one for 64 bytes
+    int gather = -1;
+    int64_t best = 0, gather_tiles = 0;
     for (int t = 0; t < kGatherNumTiles; ++t) {
       const GatherTile& g = kGatherTiles[t];
+      if (gather_lds_bytes(g.bm, g.bn, g.kg, g.ns) > dev.lds_per_block) continue;
       const int64_t n = ((p.M + g.bm - 1) / g.bm) * ((p.N + g.bn - 1) / g.bn);
       const int64_t cost = (n + dev.num_cus - 1) / dev.num_cus * (g.bn * 64 / d + g.bm * 2);
-      if (out->gather < 0 || cost < best) {
+      if (gather < 0 || cost < best) {
         best = cost;
-        out->gather = t;
-        tiles = n;
+        gather = t;
+        gather_tiles = n;
       }
     }
-    min_chunks = kGatherMinSplitChunks;
+    if (gather >= 0 && gather_faster(p, dev, tile, tiles, gather, gather_tiles)) {
+      out->gather = gather;
+      tiles = gather_tiles;
+      min_chunks = kGatherMinSplitChunks;
+    }
   }
   int ksplit = 1;
   const int64_t chunks = p.K / kGemmKC;

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(kGatherThreads) void k_gemm_gather(GemmArgs a) {
   constexpr int TPC = 64 / RUN;                // threads per column
   constexpr int IPT = RUN / D > 0 ? RUN / D : 1;       // ids per thread and chunk
   constexpr int HPI = RUN < D ? RUN : D;               // halves taken of each codeword
-  constexpr int NW = (RUN + 1) / 2;                    // dwords per run
+  constexpr int NW = HPI == 1 ? RUN : RUN / 2;         // dwords per run in flight (single halves: one each)
   constexpr int IDB = (IPT * BITS + 7) / 8;            // id bytes per run (12-bit ids: of an even id, or one id's two)
   static_assert((NS - 2) * (IPT + 1 + XI) < 64, "more loads in flight than the counter holds");
   static_assert(FM >= 1 && RUN % HPI == 0 && RUN * kGatherThreads == BN * 64, "tile does not split over the threads");
@@ -99,25 +99,41 @@ __global__ __launch_bounds__(kGatherThreads) void k_gemm_gather(GemmArgs a) {
   const int col = tid / TPC, part = tid % TPC;
   const uint8_t* idrow = a.idx + (n0 + col < a.N ? n0 + col : 0) * a.R;
   const int bdst = col * 128 + (((part * RUN) / 8) ^ ((col >> 1) & 7)) * 16 + (part * RUN) % 8 * 2;
+  // Ids and codewords stay as their loads leave them until they are used, steps
+  // later: arithmetic on them here would wait for the load.
   struct Ids {
-    uint32_t w[(IDB + 3) / 4 > 0 ? (IDB + 3) / 4 : 1];
+    uint32_t w[IDB == 3 ? 2 : (IDB + 3) / 4];
   };
+  const int odd = BITS == 12 && IPT == 1 ? (part * RUN / D & 1) * 4 : 0;  // the id starts at half a byte
   auto load_ids = [&](Ids& o, int c) {
     const int s = chunk_of(c) * (kGemmKC / D) + part * RUN / D;  // first id of the run
-    o.w[(IDB + 3) / 4 - 1] = 0;
-    __builtin_memcpy(o.w, idrow + (int64_t)s * BITS / 8, IDB);
-    if constexpr (BITS == 12 && IPT == 1) o.w[0] = (s & 1) ? o.w[0] >> 4 : o.w[0] & 0xFFFu;
+    const uint8_t* at = idrow + (int64_t)s * BITS / 8;
+    if constexpr (IDB == 3) {
+      o.w[0] = 0;
+      __builtin_memcpy(o.w, at, 2);
+      o.w[1] = at[2];
+    } else {
+      o.w[(IDB + 3) / 4 - 1] = 0;
+      __builtin_memcpy(o.w, at, IDB);
+    }
   };
   struct Words {
     uint32_t w[NW];
   };
-  auto gather_run = [&](Words& o, const Ids& ids) {
+  // The codewords of chunk c.  Past the last chunk every lane reads codeword 0:
+  // the loads the waits count stay, the random reads don't.
+  auto gather_run = [&](Words& o, const Ids& ids, int c) {
+    uint32_t w[(IDB + 3) / 4];
+#pragma unroll
+    for (int i = 0; i < (IDB + 3) / 4; ++i) {
+      const uint32_t raw = IDB == 3 ? ids.w[0] | (ids.w[1] << 16) : ids.w[i] >> odd;
+      w[i] = raw & (c < nchunks ? ~0u : 0u);
+    }
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
-      const half_t* src = a.cb + (size_t)stream_id<BITS>(ids.w, i) * D + (RUN < D ? part * RUN % D : 0);
+      const half_t* src = a.cb + (size_t)stream_id<BITS>(w, i) * D + (RUN < D ? part * RUN % D : 0);
       if constexpr (HPI == 1) {
-        const uint32_t v = *reinterpret_cast<const uint16_t*>(src);
-        o.w[i / 2] = i % 2 ? o.w[i / 2] | (v << 16) : v;
+        o.w[i] = *reinterpret_cast<const uint16_t*>(src);
       } else if constexpr (HPI == 2) {
         o.w[i] = *reinterpret_cast<const uint32_t*>(src);
       } else if constexpr (HPI == 4) {
@@ -131,8 +147,11 @@ __global__ __launch_bounds__(kGatherThreads) void k_gemm_gather(GemmArgs a) {
   };
   auto store_run = [&](const Words& o, int buffer) {
     uint8_t* p = btile + buffer * (BN * 128) + bdst;
-    if constexpr (NW == 2) *reinterpret_cast<u32x2*>(p) = u32x2{o.w[0], o.w[1]};
-    else *reinterpret_cast<u32x4*>(p) = u32x4{o.w[0], o.w[1], o.w[2], o.w[3]};
+    uint32_t v[RUN / 2];
+#pragma unroll
+    for (int i = 0; i < RUN / 2; ++i) v[i] = HPI == 1 ? o.w[2 * i] | (o.w[2 * i + 1] << 16) : o.w[i];
+    if constexpr (RUN == 4) *reinterpret_cast<u32x2*>(p) = u32x2{v[0], v[1]};
+    else *reinterpret_cast<u32x4*>(p) = u32x4{v[0], v[1], v[2], v[3]};
   };
 
   float16_t acc[FM];
@@ -151,47 +170,50 @@ __global__ __launch_bounds__(kGatherThreads) void k_gemm_gather(GemmArgs a) {
   for (int q = 0; q < NS - 1; ++q) copy_x(q, q);
 #pragma unroll
   for (int q = 0; q < NS; ++q) {
-    gather_run(cw[q], ids[q]);
+    gather_run(cw[q], ids[q], q);
     load_ids(ids[q], q + NS);
   }
   store_run(cw[0], 0);
-  gather_run(cw[0], ids[0]);
+  gather_run(cw[0], ids[0], NS);
   load_ids(ids[0], 2 * NS);
   wait_vmcnt<0>();
   wait_lgkmcnt0();
   __builtin_amdgcn_s_barrier();
 
-  for (int c0 = 0; c0 < nchunks; c0 += NS) {
+  // chunk c from ring slot u = c % NS
+  auto multiply = [&](int c, int u) __attribute__((always_inline)) {
+    const uint8_t* xb = xring + u * (BM * 128);
+    const uint8_t* bb = btile + (c % NB) * (BN * 128);
+    const int bc = wn * 32 + l32;
+    half8_t av[STEPS][FM], bv[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+      const int g = (s * KG + kg) * 2 + h;  // 16-byte granule of the row
+      bv[s] = *reinterpret_cast<const half8_t*>(bb + bc * 128 + (g ^ ((bc >> 1) & 7)) * 16);
+#pragma unroll
+      for (int f = 0; f < FM; ++f) {
+        const int r = (wm * FM + f) * 32 + l32;
+        av[s][f] = *reinterpret_cast<const half8_t*>(xb + r * 128 + (g ^ ((r >> 1) & 7)) * 16);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+      for (int f = 0; f < FM; ++f)
+        acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[s][f], bv[s], acc[f], 0, 0, 0);
+  };
+  int c0 = 0;
+  for (; c0 + NS <= nchunks; c0 += NS) {  // whole turns of the ring
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
       const int c = c0 + u;
       const int slot = (u + 1) % NS;  // of chunks c + 1, c + 1 + NS, c + 1 + 2 NS
       store_run(cw[slot], (c + 1) % NB);
-      gather_run(cw[slot], ids[slot]);
+      gather_run(cw[slot], ids[slot], c + 1 + NS);
       load_ids(ids[slot], c + 1 + 2 * NS);
       copy_x(c + NS - 1, (u + NS - 1) % NS);
       __builtin_amdgcn_sched_barrier(0);
-      if (c < nchunks) {
-        const uint8_t* xb = xring + u * (BM * 128);
-        const uint8_t* bb = btile + (c % NB) * (BN * 128);
-        const int bc = wn * 32 + l32;
-        half8_t av[STEPS][FM], bv[STEPS];
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-          const int g = (s * KG + kg) * 2 + h;  // 16-byte granule of the row
-          bv[s] = *reinterpret_cast<const half8_t*>(bb + bc * 128 + (g ^ ((bc >> 1) & 7)) * 16);
-#pragma unroll
-          for (int f = 0; f < FM; ++f) {
-            const int r = (wm * FM + f) * 32 + l32;
-            av[s][f] = *reinterpret_cast<const half8_t*>(xb + r * 128 + (g ^ ((r >> 1) & 7)) * 16);
-          }
-        }
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s)
-#pragma unroll
-          for (int f = 0; f < FM; ++f)
-            acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[s][f], bv[s], acc[f], 0, 0, 0);
-      }
+      multiply(c, u);
       __builtin_amdgcn_sched_barrier(0);
       // this wave's X copies of chunk c + 1 (after them each of NS - 2 steps
       // issued at least IPT gathers, one id load and XI copies) and its
@@ -202,7 +224,16 @@ __global__ __launch_bounds__(kGatherThreads) void k_gemm_gather(GemmArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  wait_vmcnt<0>();  // drain the clamped copies issued past the last chunk
+  wait_vmcnt<0>();  // what is left is in the ring and the registers (the clamped copies past it too)
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int u = 0; u < NS - 1; ++u) {  // fewer chunks than a turn
+    if (c0 + u >= nchunks) break;
+    store_run(cw[u + 1], (c0 + u + 1) % NB);
+    multiply(c0 + u, u);
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
+  }
 
   if constexpr (KG > 1) {
     // groups 1 .. KG - 1 leave their accumulators in LDS, group 0 adds them in order

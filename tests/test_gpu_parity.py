@@ -166,7 +166,7 @@ def test_gemm_tile_choice():
     assert fasq.plan("gemm", 512, 4096, 14336, 8, 4, 256).startswith("k_gemm_mfma<8, 4, 0, 128, 256, 2, 4, ")
     # sub-vectors of 1 or 2, or 16-bit ids, would spill in the big tile
     assert fasq.plan("gemm", 2048, 4096, 14336, 8, 2, 256).startswith("k_gemm_mfma<8, 2, 0, 128, 256, ")
-    assert fasq.plan("gemm", 2048, 4096, 14336, 16, 4, 65536).startswith("k_gemm_mfma<16, 4, 2, 128, 256, ")
+    assert fasq.plan("gemm", 2048, 4096, 14336, 16, 2, 5000).startswith("k_gemm_mfma<16, 2, 1, 128, 256, ")
 
 
 @pytest.mark.parametrize("case", [(777, 448, 12345, 4, 256, 8), (600, 384, 16400, 4, 4096, 12)])

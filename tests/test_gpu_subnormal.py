@@ -136,18 +136,29 @@ GEMM_PATHS = [
     ((64, 128), (500, 256, 3000, 4, 256, 8)),
     ((64, 64), (40, 320, 100, 4, 256, 8)),
     ((64, 128), (130, 256, 257, 4, 4096, 12)),   # 12-bit ids: the 64 x 64 tile cannot split its id copies evenly
-    ((64, 64), (100, 1088, 70, 4, 65536, 16)),
+    ((64, 64), (100, 128, 70, 4, 251, 8)),        # codebook in global memory
+]
+
+# the same for codebooks gathered from global memory
+GATHER_PATHS = [
+    ((64, 32), (100, 1088, 70, 4, 65536, 16)),
+    ((128, 32), (250, 192, 4096, 2, 40000, 16)),
+    ((256, 32), (300, 320, 3000, 1, 65536, 16)),
+    ((256, 64), (1000, 192, 4000, 8, 9000, 16)),
 ]
 
 
 @pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("path", GEMM_PATHS, ids=lambda p: f"{p[0][0]}x{p[0][1]}-{p[1]}")
+@pytest.mark.parametrize("path", GEMM_PATHS + GATHER_PATHS, ids=lambda p: f"{p[0][0]}x{p[0][1]}-{p[1]}")
 def test_gemm_tiles(path, kind):
     tile, (M, K, N, d, C, bits) = path
     label = f"gemm tile {tile} {path[1]} {kind}"
     print(f"[case] {label}", flush=True)
     base, params = parse_plan(fasq.plan("gemm", M, K, N, bits, d, C))
-    assert base == "k_gemm_mfma" and tuple(params[3:5]) == tile, (label, params)
+    if path in GATHER_PATHS:
+        assert base == "k_gemm_gather" and tuple(params[2:4]) == tile, (label, base, params)
+    else:
+        assert base == "k_gemm_mfma" and tuple(params[3:5]) == tile, (label, base, params)
     x, cb, ids = draw(kind, M, K, N, d, C, seed=M + K + N + C + 1)
     idx = pi.pack_indices(ids, bits)
     y = to_np(fasq.pq_gemm(to_dev(x), to_dev(idx), bits, d, to_dev(cb)))
