@@ -253,7 +253,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64) void k_gemm_mfma(GemmArgs a) {
   // tokens 44.3 / 41.4, 4096 x 14336 at 128 tokens 44.0 / 41.0.  At d = 4
   // (64 x 128 tile) the chunk is 2 to 9 % slower (512 tokens 27.9 / 29.2), at
   // d = 1 0 to 5 %.
-  constexpr bool kChunkAhead = WAVES == 4 && FM * FN <= 2 && D == 2;
+  constexpr bool kChunkAhead = WAVES == 4 && FM * FN <= 2 && D == 2 && MODE != CB_GLOBAL;
   if constexpr (kChunkAhead) {
     Ops o[4];
 #pragma unroll
@@ -275,6 +275,7 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64) void k_gemm_mfma(GemmArgs a) {
               acc[fm][fn] = __builtin_amdgcn_mfma_f32_32x32x16_f16(o[t].a[fm], o[t].b[fn], acc[fm][fn], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
+      if (c + 1 == niter) break;
 #pragma unroll
       for (int t = 0; t < 4; ++t) read_ops(o[t], nstage, idn, t);
     }
