@@ -84,7 +84,7 @@ constexpr int kGemvPipe = 8;      // load slots per wave of the row-streaming ke
 // or two banks when M is even, and the final sum's reads hit one.
 __host__ __device__ constexpr int gemv_red_stride(int P) { return P > 1 ? P + 1 : 1; }
 // Index loads each wave of the 16-row-tile kernel keeps in flight (see
-// kM1Window), none of them past its last unit.  With seven, the units past
+// kM1Window), none of them past its last unit (but see kClampedTail).  With seven, the units past
 // the end loading one address, o_proj (4096 x 4096, d = 2, C = 256) took 1.7 us
 // longer: the waves end only when those loads are back.
 constexpr int kGemvWindow = 2;
@@ -118,7 +118,13 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   constexpr int SPC = G * D / 8;         // MFMA steps (8 K values each) per chunk
   constexpr int XCB = G * D * 2;         // bytes of x per chunk column and token
   constexpr int L = T > 4 ? T : 4;       // load slots, units per unrolled group
-  constexpr int W = kGemvWindow;         // index loads in flight per wave
+  // 8-bit ids at d = 4 and 8 leave a slab one to four units per wave.  There
+  // one loop whose loads go on past the last unit (to the table's first
+  // chunk), three in flight, beats code made for each remainder: 5 tokens,
+  // 17216 x 1844, d = 4 16.5 against 20.5 us, d = 8, 14848 x 5537 at 10 tokens 24.8
+  // against 29.2; at d = 1 and 2 and with wider ids it is 1 to 8 % slower.
+  constexpr bool kClampedTail = SLAB && BITS == 8 && D >= 4;
+  constexpr int W = kClampedTail ? L - 1 : kGemvWindow;  // index loads in flight per wave
   static_assert(L % T == 0 && W < L, "load slots must cover the window and whole tiles");
   static_assert(MR == 16, "16 token slots");
   static_assert(!SLAB || MASK, "slabs take the column checks");
@@ -194,8 +200,8 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
   // index stream is already in flight.
   const uint32_t lane_off = repl_lane_off<D>(lane);
   // A operands (x) live in registers when they fit (x staged whole, no
-  // masked columns), loaded straight from global memory with the codebook
-  // (x takes no LDS then); else x is staged in LDS, a slab at a time, and
+  // masked columns), brought there by way of LDS (below) while the codebook
+  // is loaded (x keeps no LDS then); else x is staged in LDS, a slab at a time, and
   // read at every step.  Rows of A past M repeat a real row.
   constexpr bool kXInRegs = !MASK && T * SPC <= 8;
   const int mrow = nl < M ? nl : M - 1;  // x row this lane feeds to the A operand
@@ -399,36 +405,43 @@ __global__ __launch_bounds__(1024) void k_gemv(GemvArgs a) {
     // whose loads all lie within the wave's units, then the last R < L + W
     // units in code made for R (see the row-streaming kernel below: a test
     // around each load would make the compiler wait for all of them).
-    int base = 0;
-    for (; base + L + W <= nunits; base += L) {
+    if constexpr (kClampedTail) {
+      for (int base = 0; base < nunits; base += L) {
 #pragma unroll
-      for (int i = 0; i < L; ++i) {
-        load_unit((i + W) % L, base + i + W, (i + W) % T);
-        compute(i, base + i, i % T);
+        for (int i = 0; i < L; ++i) {
+          load_unit((i + W) % L, base + i + W, (i + W) % T);
+          if (base + i < nunits) compute(i, base + i, i % T);
+        }
       }
-    }
-    auto last = [&](auto rc) __attribute__((always_inline)) {
-      constexpr int R = decltype(rc)::value;
+    } else {
+      int base = 0;
+      for (; base + L + W <= nunits; base += L) {
 #pragma unroll
-      for (int i = 0; i < R; ++i) {
-        if (i + W < R) load_unit((i + W) % L, base + i + W, (i + W) % T);
-        compute(i % L, base + i, i % T);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < L; ++i) {
+          load_unit((i + W) % L, base + i + W, (i + W) % T);
+          compute(i, base + i, i % T);
+        }
       }
-    };
-    // nunits is a multiple of T, and so is the rest
-    static_assert(L + W - 1 <= 9, "one case per possible remainder");
-    switch (nunits - base) {
-      case 1: if constexpr (1 % T == 0) last(std::integral_constant<int, 1>{}); break;
-      case 2: if constexpr (2 % T == 0) last(std::integral_constant<int, 2>{}); break;
-      case 3: if constexpr (3 % T == 0) last(std::integral_constant<int, 3>{}); break;
-      case 4: if constexpr (4 % T == 0) last(std::integral_constant<int, 4>{}); break;
-      case 5: if constexpr (5 % T == 0) last(std::integral_constant<int, 5>{}); break;
-      case 6: if constexpr (6 % T == 0 && L + W > 6) last(std::integral_constant<int, 6>{}); break;
-      case 7: if constexpr (7 % T == 0 && L + W > 7) last(std::integral_constant<int, 7>{}); break;
-      case 8: if constexpr (8 % T == 0 && L + W > 8) last(std::integral_constant<int, 8>{}); break;
-      case 9: if constexpr (9 % T == 0 && L + W > 9) last(std::integral_constant<int, 9>{}); break;
-      default: break;
+      auto last = [&](auto rc) __attribute__((always_inline)) {
+        constexpr int R = decltype(rc)::value;
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          if (i + W < R) load_unit((i + W) % L, base + i + W, (i + W) % T);
+          compute(i % L, base + i, i % T);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      // nunits is a multiple of T, and so is the rest
+      static_assert(T == 8 ? L == 8 && W < 8 : L == 4 && W <= 2, "one case per possible remainder");
+      switch (nunits - base) {
+        case 1: if constexpr (1 % T == 0) last(std::integral_constant<int, 1>{}); break;
+        case 2: if constexpr (2 % T == 0) last(std::integral_constant<int, 2>{}); break;
+        case 3: if constexpr (3 % T == 0) last(std::integral_constant<int, 3>{}); break;
+        case 4: if constexpr (4 % T == 0) last(std::integral_constant<int, 4>{}); break;
+        case 5: if constexpr (5 % T == 0) last(std::integral_constant<int, 5>{}); break;
+        case 8: if constexpr (T == 8) last(std::integral_constant<int, 8>{}); break;
+        default: break;
+      }
     }
   }
   if (rounds) return;

@@ -93,3 +93,49 @@ def test_segments_with_x_in_registers(case):
     p = pi.draw_problem(rng, M, K, N, d, C, bits)
     y = to_np(fasq.pq_gemv_ex(to_dev(p.x), to_dev(p.idx), bits, d, to_dev(p.codebook), workspace=ws)).astype(np.float64)
     assert_close(y[:, rows], orc.pq_linear(p.x, p.idx, bits, d, p.codebook, rows=rows), str(case))
+
+
+def test_a_workspace_too_small_for_the_segments_takes_the_gemm():
+    """From 12 tokens on a workspace that holds the GEMM's K split but not the
+    decode kernel's segments gives the GEMM's bits; one byte less than that
+    gives the decode kernel's without a split; the full one its segments."""
+    rng = np.random.default_rng(31)
+    M, K, N, d, C, bits = 16, 14336, 5000, 2, 256, 8
+    need, gemm_need = (f(M, K, N, bits, d, C, *a) for f, a in ((fasq.gemv_ex_workspace_bytes, (0,)),
+                                                               (fasq.gemm_ex_workspace_bytes, ())))
+    assert need == 4 * M * N * 4 and 0 < gemm_need < need
+    p = pi.draw_problem(rng, M, K, N, d, C, bits)
+    args = (to_dev(p.x), to_dev(p.idx), bits, d, to_dev(p.codebook))
+
+    def call(nbytes):
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda:0")
+        return fasq.pq_gemv_ex(*args, workspace=ws).view(torch.int16)
+
+    rows = sample_rows(N, 200)
+    ref = orc.pq_linear(p.x, p.idx, bits, d, p.codebook, rows=rows)
+    for nbytes in (need, gemm_need, gemm_need - 1):
+        assert_close(to_np(call(nbytes).view(torch.float16))[:, rows].astype(np.float64), ref, f"workspace {nbytes}")
+    assert torch.equal(call(gemm_need), fasq.pq_gemm_ex(*args).view(torch.int16))
+    assert torch.equal(call(gemm_need - 1), fasq.pq_gemv(*args).view(torch.int16))
+
+
+SLABS = [
+    # M, K, N, d, C, bits: one to several units per wave and slab, masked columns
+    (5, 17216, 261, 4, 256, 8),
+    (7, 10944, 4600, 4, 256, 8),
+    (8, 14080, 33000, 4, 256, 8),
+    (13, 19200, 1209, 8, 256, 8),
+    (10, 11648, 20500, 8, 256, 8),
+]
+
+
+@pytest.mark.parametrize("case", SLABS)
+def test_slabs_of_long_rows(case):
+    M, K, N, d, C, bits = case
+    print(f"[case] decode slabs {case}", flush=True)
+    assert fasq.plan("gemv", M, K, N, bits, d, C).endswith(", 1, 1>"), fasq.plan("gemv", M, K, N, bits, d, C)
+    rng = np.random.default_rng(sum(case))
+    x, idx, cb = exact_problem(rng, M, K, N, d, C, bits)
+    y = to_np(fasq.pq_gemv(to_dev(x), to_dev(idx), bits, d, to_dev(cb))).astype(np.float64)
+    rows = np.unique(np.concatenate([sample_rows(N, 100), np.arange(N - 20, N)]))
+    assert np.array_equal(y[:, rows], orc.pq_linear(x, idx, bits, d, cb, rows=rows))
