@@ -119,3 +119,29 @@ def test_general_kernel_is_exact_on_small_integers(monkeypatch):
     x = pi.ternary_x(rng, M, K)
     y = to_np(fasq.pq_gemv_ex(to_dev(x), to_dev(pi.pack_indices(ids, bits)), bits, d, to_dev(books)))
     assert np.array_equal(y.astype(np.float64), orc.lut_accumulate(x, books, ids.T))
+
+
+@pytest.mark.parametrize("case", [(37, 1516, 40, 4, 256, 8), (18, 99, 70, 3, 256, 8), (20, 130, 31, 1, 64, 8),
+                                  (20, 160, 30, 40, 90, 12), (2, 65, 7, 1, 300, 12), (33, 264, 50, 8, 300, 12)])
+@pytest.mark.parametrize("per", [False, True])
+def test_infinities_and_nan_reach_only_their_outputs(case, per, monkeypatch):
+    """Non-finite codewords and activations, also beside the zeros that fill a
+    run past the row's end: the oracle's outputs, infinities and NaN included."""
+    monkeypatch.setenv("FASQ_FORCE_PATH", "generic")
+    M, K, N, d, C, bits = case
+    rng = np.random.default_rng(sum(case) + per)
+    S = K // d
+    books = np.stack([pi.signed_one_hot_codebook(C, d, rng) for _ in range(S if per else 1)])
+    ids = rng.integers(3, C, size=(N, S))
+    ids[N // 2, 0], ids[N - 1, S - 1], ids[0, S // 2] = 0, 1, 2
+    books[:, 0], books[:, 1], books[:, 2] = np.inf, -np.inf, np.nan
+    x = pi.ternary_x(rng, M, K)
+    x[0, K - 1], x[M - 1, 0] = np.inf, -np.inf
+    if M > 2:
+        x[M // 2, K // 2] = np.nan
+    idx = pi.pack_indices(ids, bits)
+    with np.errstate(invalid="ignore"):
+        ref = orc.lut_accumulate(x, books, ids.T) if per else orc.pq_linear(x, idx, bits, d, books[0])
+    cb = to_dev(books if per else books[0])
+    y = to_np(fasq.pq_gemv_ex(to_dev(x), to_dev(idx), bits, d, cb)).astype(np.float64)
+    assert np.array_equal(y, ref, equal_nan=True)

@@ -30,7 +30,7 @@ import pytest
 
 import pq_inputs as pi
 from oracle import pq_oracle as orc
-from gpu_util import to_dev, to_np
+from gpu_util import sample_rows, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -125,6 +125,32 @@ def test_gemv_paths(path, kind):
     idx = pi.pack_indices(ids, bits)
     y = to_np(fasq.pq_gemv(to_dev(x), to_dev(idx), bits, d, to_dev(cb)))
     check_exact(y, orc.pq_linear(x, idx, bits, d, cb), kind, label)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_gemv_rounds_of_tiles(kind):
+    """The decode kernel summing its tiles in rounds (its plan ends in 0, 0, 1)."""
+    M, K, N, d, C, bits = 16, 2048, 50000, 4, 256, 8
+    assert fasq.plan("gemv", M, K, N, bits, d, C).endswith(", 0, 0, 1>")
+    x, cb, ids = draw(kind, M, K, N, d, C, seed=77)
+    idx = pi.pack_indices(ids, bits)
+    y = to_np(fasq.pq_gemv(to_dev(x), to_dev(idx), bits, d, to_dev(cb)))
+    rows = sample_rows(N, 200)
+    check_exact(y[:, rows], orc.pq_linear(x, idx, bits, d, cb, rows=rows), kind, f"gemv rounds {kind}")
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("case", [(16, 14336, 4096, 2, 256, 8), (5, 14336, 77, 4, 256, 8)])
+def test_gemv_segments_with_x_in_registers(case, kind):
+    """The decode kernel with K split over workgroups, each segment's x in registers."""
+    M, K, N, d, C, bits = case
+    need = fasq.gemv_ex_workspace_bytes(M, K, N, bits, d, C, 0)
+    assert need == 4 * M * N * 4
+    x, cb, ids = draw(kind, M, K, N, d, C, seed=M + N)
+    idx = pi.pack_indices(ids, bits)
+    y = to_np(fasq.pq_gemv_ex(to_dev(x), to_dev(idx), bits, d, to_dev(cb)))
+    rows = sample_rows(N, 200)
+    check_exact(y[:, rows], orc.pq_linear(x, idx, bits, d, cb, rows=rows), kind, f"gemv segments {case} {kind}")
 
 
 # fasq_pq_gemm tiles: (rows, columns) of the output tile, (M, K, N, d, C, bits)
