@@ -32,7 +32,8 @@ Algorithmic bytes of one GEMV: N*R (packed ids) + C*d*2 (codebook) +
 M*K*2 (x) + M*N*2 (y), with x counted once per grouped launch; flops of one
 GEMM: 2*M*N*K.
 
-Prints ONE JSON line on stdout; progress goes to stderr.
+Prints ONE JSON line on stdout (without the sweeps' tables, which --out
+writes too); progress goes to stderr.
 """
 
 from __future__ import annotations
@@ -1302,6 +1303,21 @@ def report_layer(tag, res):
         f"kernel sum {res['us_per_layer_kernel_sum']:.2f} us ({res['gbs_kernel_sum']:.1f} GB/s)")
 
 
+def printed(record):
+    """The record as the one line on stdout: floats to six digits, without the
+    sweeps' tables (stderr has their figures, ``--out`` the whole record), so
+    that the line stays short enough to be read from the end of a log."""
+    def short(v):
+        if isinstance(v, float):
+            return float(f"{v:.6g}")
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items()}
+        return [short(x) for x in v] if isinstance(v, (list, tuple)) else v
+
+    extra = {k: v for k, v in record["extra"].items() if k not in ("crossover", "sensitivity")}
+    return short({**record, "extra": extra})
+
+
 def main():
     ap = argparse.ArgumentParser(description=__doc__.split("\n")[0])
     ap.add_argument("--gpus", type=int, default=1)
@@ -1467,11 +1483,10 @@ def main():
         best = max(extra["prefill"], key=lambda r: r["tflops"])
         record["prefill_tflops_best"] = best["tflops"]
         record["prefill_best_config"] = f"{best['name']} M={best['M']}"
-    line = json.dumps(record)
-    print(line, flush=True)
     if args.out:
         with open(args.out, "w") as f:
-            f.write(line + "\n")
+            f.write(json.dumps(record) + "\n")
+    print(json.dumps(printed(record)), flush=True)
 
 
 if __name__ == "__main__":
