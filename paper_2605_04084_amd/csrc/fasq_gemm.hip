@@ -223,9 +223,8 @@ bool gemm_plan(const Problem& p, const DeviceInfo& dev, GemmPlan* out) {
   int64_t min_chunks = (int64_t)kGemmMinSplitChunks * kg;
   out->gather = -1;
   if (mode == CB_GLOBAL) {
-    // the tile with the fewest address cycles over its rounds of workgroups: a
-    // gather takes one a lane (two from L2 on end, see k_gemm_gather; the X
-    // copies wait in the same queue), the X copy one for 64 bytes
+    // the tile with the fewest address cycles over its rounds of workgroups:
+    // one for each lane's gather, one for 64 bytes of the X copy
     int gather = -1;
     int64_t best = 0, gather_tiles = 0;
     for (int t = 0; t < kGatherNumTiles; ++t) {

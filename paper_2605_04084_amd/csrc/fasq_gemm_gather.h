@@ -1,16 +1,18 @@
 // Prefill GEMM for codebooks gathered from global memory (L2): Y[M x N] =
 // X[M x K] . W_hat^T with every W_hat tile decoded once per workgroup.
 //
-// Bound by the gathers: a CU reads random codewords at about one lane per
-// cycle, whatever its waves do meanwhile.  k_gemm_mfma gathers each B operand
+// Bound by the gathers: a CU's address units take one lane of a random read per
+// cycle, and from L2 the card serves about half of that (278 G reads/s in a
+// probe, 0.45 per cycle and CU).  k_gemm_mfma gathers each B operand
 // in every wave row that uses it; here the workgroup decodes the BN x 64 tile
 // of each K chunk once into LDS, all waves read their operands from there,
 // and a tall tile (BM rows of X for few columns) re-gathers W_hat for few
 // row tiles.  4096 x 4096, 65536 entries, d = 4, 512 tokens: 244 -> 61 us; the
 // address units are then busy 73 % of the time (half of it the gathers, most
-// of the rest the X copy).  Cycles per chunk and workgroup: BN * 64 / d gathers plus
-// BM * 128 / 64 for the X copy; the launcher takes the tile with the smallest
-// sum over its rounds.
+// of the rest the X copy).  Address cycles per chunk and workgroup: BN * 64 / d
+// for the gathers plus BM * 128 / 64 for the X copy; the launcher takes the
+// tile with the smallest sum over its rounds (a ranking of tiles: the time
+// itself is that of the reads from L2).
 //
 // Pipeline, one chunk of 64 K values per step, NS slots: at step c the
 // codewords of chunk c + 1 (gathered since step c + 1 - NS) go to LDS, the
@@ -18,7 +20,8 @@
 // issued, then the X copy of chunk c + NS - 1 (global_load_lds, ring of NS),
 // then the MFMAs of chunk c; one barrier per step.  Loads return in order, so
 // waiting for the X copy of the next chunk leaves the loads of NS - 2 steps
-// in flight.  KG wave groups share the k-steps of a chunk
+// in flight.  Chunks past the last one read codeword 0, and the last chunks
+// that fill no turn of the ring run without loads.  KG wave groups share the k-steps of a chunk
 // where the tile has fewer than eight 32 x 32 blocks; their accumulators are
 // added through LDS in group order.
 #pragma once

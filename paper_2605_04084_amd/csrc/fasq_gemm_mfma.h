@@ -245,11 +245,12 @@ __global__ __launch_bounds__(WGM * WGN * KG * 64) void k_gemm_mfma(GemmArgs a) {
   uint32_t idc[FN][HB / 4], idn[FN][HB / 4];
   read_ids(0, idc);
   // At d = 2 (four gathers per operand) tiles whose waves hold one or two MFMA
-  // blocks read a whole chunk ahead instead: a
+  // blocks read a whole chunk ahead instead (but not from global memory, where
+  // that is 16 random reads in flight per lane: 64 x 119 at 23 tokens 6.1 / 7.9 us): a
   // k-step there is 32 or 64 cycles of MFMA behind an LDS round trip, so four
   // steps in turn cost four of them.  The reads of chunk c + 1 follow the
   // MFMAs of chunk c, and its ids are read before them.  d = 2, C = 256, us,
-  // step by step / a chunk ahead: 4096 x 4096 at 128 tokens 18.2 / 17.8, 512
+  // step by step / a chunk ahead: 4096 x 4096 at 128 tokens 17.8 / 16.7, 512
   // tokens 44.3 / 41.4, 4096 x 14336 at 128 tokens 44.0 / 41.0.  At d = 4
   // (64 x 128 tile) the chunk is 2 to 9 % slower (512 tokens 27.9 / 29.2), at
   // d = 1 0 to 5 %.

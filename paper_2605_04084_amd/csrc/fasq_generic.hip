@@ -42,14 +42,14 @@ __global__ __launch_bounds__(256) void k_reconstruct(const uint8_t* __restrict__
 // ids as one run and the gathered codewords serve every token of the
 // workgroup.  The K order inside a span is permuted identically for both
 // operands.
-// Bound by the gathers: one lane per cycle and CU from global memory, where
-// LDS serves ten and more, hence LCB: a shared codebook of up to
+// Bound by the gathers: at most one lane per cycle and CU from global memory
+// (half of that from L2), where LDS serves ten and more, hence LCB: a shared codebook of up to
 // kGenericLdsBytes is staged in LDS.  With a codebook per subspace the 16
 // features of a group share the few cache lines of one book, so a workgroup
 // draws about every book through its L1 once (2 MB for 4096 x 4096 at d = 2,
 // C = 256).  Measured against one wave per feature with scalar products:
-// 48 tokens of that layer 694 -> 34 us, one token 52 -> 18 us; 1003 x 1516,
-// d = 4, 37 tokens 84 -> 7 us (kernel).
+// 48 tokens of that layer 694 -> 30 us, one token 52 -> 18 us; 1003 x 1516,
+// d = 4, 37 tokens 84 -> 5 us.
 // D: d as a compile-time constant, or 0 for any other d.
 constexpr int kGenericRun = 32;     // K values per lane and wave step, at most
 constexpr int kGenericWaves = 16;   // most waves per workgroup
