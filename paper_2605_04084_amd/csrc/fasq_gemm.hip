@@ -255,15 +255,19 @@ bool gemm_plan(const Problem& p, const DeviceInfo& dev, GemmPlan* out) {
   return true;
 }
 
-// Whether a decode call with a workspace runs faster on this GEMM: from 12
-// tokens on, when the decode kernel would have to stage x in slabs (rows of
-// x too long for LDS) and the GEMM splits K with its codebook in LDS.
-// Measured on the Llama-3-8B down_proj shape (4096 x 14336, d = 2, C = 256):
-// 12 tokens 29.3 us on the decode kernel against 25.6 us on the GEMM, 16
-// tokens 35.7 against 26.5 us (8 tokens: 22.0 against 26.6); with x whole in
-// LDS or registers (gate_proj 16 tokens: 15.9 against 25.3 us), or a
-// codebook the GEMM has to gather from global memory (65536 entries), the
-// decode kernel is the faster one.
+// Whether a decode call with a workspace goes to this GEMM: from 12 tokens on,
+// when the decode kernel would stage x in slabs (rows of x too long for LDS),
+// the GEMM splits K with its codebook in LDS, and the decode kernel's K
+// segments with x in registers don't fill the CUs.
+// The line is older than the decode kernel's present index window and
+// segments, which moved it: of 1650 random calls that it sends here (K 4200 to
+// 20000, N to 16384, 12 to 16 tokens) most would be faster on the decode
+// kernel, narrow ones above all (d = 2, C = 256, 18432 x 310 at 12 tokens 17.3 here
+// against 7.1 us; 12 bits, d = 4, 18560 x 242 22.7 against 8.9), while from about 2000
+// rows on and 14 to 16 tokens the GEMM is (d = 2, 14400 x 3667 24.1 against 35.0 us;
+// 12 bits, d = 4, 7488 x 15354 32.9 against 60.4).
+// A codebook that the GEMM would gather from global memory stays with the
+// decode kernel, and so does x whole in LDS or registers.
 bool decode_prefers_gemm(const Problem& p, const DeviceInfo& dev, int64_t workspace_bytes) {
   if (p.M < kGemmFromTokens || p.M > kGemvMaxTokens || !gemv_x_slabbed(p)) return false;
   // K segments with x in registers, enough of them to fill the CUs: the decode
